@@ -43,7 +43,8 @@ HBM_PEAK_GBS = 8000.0            # MI355X HBM3E, GB/s
 ALU_PEAK_TFLOPS = 256 * 128 * 2 * 2.4e9 / 1e12
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2101_07948_amd", "csrc", f)
                   for f in ("sdnn_kernels.hip", "sdnn_host.cpp", "sdnn_internal.h",
-                            "gen_spmm_asm.py", "spmm_asm_gen.h")]
+                            "gen_spmm_asm.py", "spmm_asm_gen.h", "sdnn_quad.hip", "sdnn_quad_pack.cpp",
+                            "sdnn_device.h", "gen_quad_asm.py")]
 def traffic_file(layer: str = "w0") -> str:
     return os.path.join(ROOT, "profiles", f"traffic_spmm_{layer}.json")
 
@@ -86,7 +87,8 @@ def summarize_pmc(fetch_csv, write_csv, K, N, layer="w0"):
         copy = [(d, v) for d, k, v in rows if "elementwise" in k.lower() and "neg" in k.lower()]
         if not copy:
             raise SystemExit(f"{path}: no calibration copy dispatch")
-        spmm = [v for d, k, v in rows if "spmm_panel_kernel" in k and d < copy[0][0]]
+        spmm = [v for d, k, v in rows if d < copy[0][0] and
+                ("spmm_panel_kernel" in k or "spmm_quad_kernel" in k)]
         if not spmm:
             raise SystemExit(f"{path}: no sparse-kernel dispatch before the calibration copy")
         factor = copy_bytes / (copy[0][1] * 1024.0)   # true bytes per counted byte

@@ -58,9 +58,13 @@ typedef enum {
 } sdnn_epilogue;
 
 /* Options for sdnn_plan_create; pass NULL for the defaults {0, 1, 0, 0, NULL, 0, 0}.
- *   panel_rows:   rows per register panel.  0 (default) packs W four times, with
- *                 panels of 4, 12, 8 and 16 rows, and a fifth time with 32-row panels
- *                 for 128-column tiles unless tile_cols = 256.  sdnn_spmm picks one per
+ *   panel_rows:   rows per register panel of the panel kernel.  0 (default) packs W four
+ *                 times, with panels of 4, 12, 8 and 16 rows, and a fifth time with 32-row
+ *                 panels for 128-column tiles unless tile_cols = 256; with tile_cols = 0
+ *                 too (a default plan), also for the row-quad kernel, which then serves
+ *                 sdnn_spmm (same result bit for bit; unless sdnn_plan_tune measured the
+ *                 panel kernel faster at N).  The panel kernel, which serves the K-split
+ *                 calls and plans that fix panel_rows or tile_cols, picks one packing per
  *                 call: the 32-row panels (with 12 consumer waves per workgroup) when W
  *                 holds under 20 entries per 16 rows and 32 columns and their grid fills
  *                 the compute units; otherwise the fewest rounds of workgroups over the
@@ -131,7 +135,8 @@ typedef struct {
  * mid_* fields the third, the tallest_* fields the fourth and the deep_* fields the fifth,
  * or are 0 when the plan holds fewer packings).
  *   panels:       number of row panels (ceil(M / panel_rows)).
- *   packed_bytes: device bytes of every packed weight stream and its indexes.
+ *   packed_bytes: device bytes of the panel kernel's packed weight streams and their
+ *                 indexes.
  *   rho:          nnz / sum over panels of |union of the panel rows' column sets|,
  *                 the reuse an ideal panel kernel gets per staged B row (>= 1).
  *   fill:         nnz / stored stream entries (1.0 = no padding).
@@ -268,7 +273,7 @@ sdnn_status sdnn_spmm_split_noalloc(sdnn_plan p, const float* B, float* C, int32
                                     const float* bias, sdnn_epilogue epi, int32_t splits,
                                     void* stream);
 
-/* The launch shape sdnn_spmm uses for this plan at N columns (the tuned one if
+/* The panel kernel's launch shape for this plan at N columns (the tuned one if
  * sdnn_plan_tune recorded one for N, else the rule described under panel_rows):
  * *panel_rows = the packing's panel height, *waves = consumer waves per workgroup
  * (either pointer may be NULL).  Host only; touches no device memory.
@@ -281,7 +286,7 @@ sdnn_status sdnn_plan_launch_shape(sdnn_plan p, int32_t N, int32_t* panel_rows, 
  * splits < 0). */
 sdnn_status sdnn_plan_split_runs(sdnn_plan p, int32_t N, int32_t splits, int32_t* runs);
 
-/* The tile width (columns of C per workgroup) sdnn_spmm uses for this plan at N columns
+/* The tile width (columns of C per workgroup) of the panel kernel for this plan at N columns
  * when B and C are 16-byte aligned and N % 4 == 0 (otherwise it is 256): the tuned one if
  * sdnn_plan_tune recorded one for N, else the plan's tile_cols option, else the library's
  * rule.  Host only.  Errors: SDNN_ERR_NULL (p or tile_cols), SDNN_ERR_DIM (N <= 0, M = 0). */
@@ -291,9 +296,10 @@ sdnn_status sdnn_plan_launch_tile(sdnn_plan p, int32_t N, int32_t* tile_cols);
  * kernel implementation per operator, Sec. 3.1, and autotunes the microkernel and the
  * split-K tiling factor per sparse matrix, Sec. 3.2.2): times sdnn_spmm at this N for every
  * packing the plan holds (panel height) with several consumer-wave counts per workgroup, on
- * each tile width the call allows (256 and 128 columns, see tile_cols), on the caller's B
- * (K x N) and C (M x N, overwritten with unspecified values), and records the fastest in
- * the plan; later sdnn_spmm calls with the same N use it (up to 8 N values are kept).  For
+ * each tile width the call allows (256 and 128 columns, see tile_cols), and for every
+ * row-quad packing a default plan holds, on the caller's B (K x N) and C (M x N,
+ * overwritten with unspecified values), and records the fastest of each kernel in the plan;
+ * later sdnn_spmm calls with the same N use the faster one (up to 8 N values are kept).  For
  * a plan with K-segments it then times sdnn_spmm_split at every workgroup count along K
  * (up to 32) in a workspace it allocates for the search and frees (skipped if that
  * allocation fails), and records the fastest, one meaning the unsplit call, for

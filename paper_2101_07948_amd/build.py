@@ -8,7 +8,8 @@ import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB = os.path.join(HERE, "libsdnn.so")
-SOURCES = [os.path.join(HERE, "csrc", "sdnn_host.cpp"), os.path.join(HERE, "csrc", "sdnn_kernels.hip")]
+SOURCES = [os.path.join(HERE, "csrc", f) for f in ("sdnn_host.cpp", "sdnn_quad_pack.cpp",
+                                                   "sdnn_kernels.hip", "sdnn_quad.hip")]
 PROBES_LIB = os.path.join(HERE, "libsdnn_probes.so")
 PROBES_SOURCES = [os.path.join(HERE, "csrc", "sdnn_probes.hip")]
 
@@ -25,11 +26,13 @@ def hipcc() -> str:
 
 
 def build(verbose: bool = False) -> str:
-    # regenerate the inline-assembly inner loop (a pure function of its generator)
+    # regenerate the inline-assembly inner loops (pure functions of their generators)
     sys.path.insert(0, os.path.join(HERE, "csrc"))
     try:
+        import gen_quad_asm
         import gen_spmm_asm
         gen_spmm_asm.main()
+        gen_quad_asm.main()
     finally:
         sys.path.pop(0)
     for lib, sources in ((LIB, SOURCES), (PROBES_LIB, PROBES_SOURCES)):
@@ -46,6 +49,7 @@ def build(verbose: bool = False) -> str:
 
 
 HOST_SANITIZED_SOURCES = [os.path.join(HERE, "csrc", "sdnn_host.cpp"),
+                          os.path.join(HERE, "csrc", "sdnn_quad_pack.cpp"),
                           os.path.join(HERE, "csrc", "sdnn_launch_stubs.cpp")]
 
 

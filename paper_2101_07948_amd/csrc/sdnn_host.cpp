@@ -775,6 +775,22 @@ static int64_t packing_bytes(const Packed& P, bool narrow) {
 // Plans serve 128-column tiles unless the option fixes 256.
 static bool wants_narrow(const Options& o) { return o.tile_cols != kTileCols; }
 
+// Default plans (no panel height or tile width fixed) also hold the row-quad packings.
+static bool wants_quads(const Options& o) { return o.rws.size() > 1 && o.tile_cols == 0; }
+
+// The row of C each source row is stored to.
+static std::vector<int32_t> output_rows(const Packed& P) {
+  std::vector<int32_t> out((size_t)std::max(P.M, 1), 0);
+  for (int32_t i = 0; i < P.M; ++i) out[P.perm[i]] = P.out_permuted ? i : P.perm[i];
+  return out;
+}
+
+static int64_t quad_bytes(const QuadPacked& Q) {
+  return align256((int64_t)Q.stream.size() * 4) + align256((int64_t)Q.descs.size() * 4) +
+         align256((int64_t)(Q.progs.size() * sizeof(QuadProgram))) +
+         align256((int64_t)Q.rows.size() * 4) * 2;
+}
+
 std::vector<uint32_t> narrow_stream(const std::vector<uint32_t>& entries) {
   std::vector<uint32_t> out(entries);
   const size_t groups = entries.size() / (2 * kGroup);
@@ -870,6 +886,15 @@ sdnn_status sdnn_plan_check_host(const int32_t* row_ptr, const int32_t* col_idx,
       bytes += packing_bytes(P, wants_narrow(o));
     }
     if (o.split_chunks > 0) bytes += align256((int64_t)M * 4);  // the device copy of perm
+    if (wants_quads(o)) {
+      const std::vector<int32_t> out_row = output_rows(packs[0]);
+      for (int32_t cap : kQuadCaps) {
+        QuadPacked Q;
+        pack_quads(csr.row_ptr, csr.col_idx, csr.values, M, K, cap, out_row.data(), &Q);
+        if (!check_quads(csr.row_ptr, csr.col_idx, csr.values, M, K, out_row.data(), Q))
+          return SDNN_ERR_INTERNAL;
+      }
+    }
     if (info) fill_info(packs, bytes, o, info);
     return SDNN_OK;
   } catch (...) {
@@ -919,6 +944,17 @@ sdnn_status sdnn_plan_create(const int32_t* row_ptr, const int32_t* col_idx, con
     const int64_t perm_off = total;
     if (o.split_chunks > 0) total += align256((int64_t)M * 4);
     plan->packed_bytes = total;
+    // the row-quad packings follow (packed_bytes counts the panel packings alone)
+    std::vector<QuadPacked> quads;
+    const int64_t quad_off = total;
+    if (wants_quads(o) && M > 0) {
+      const std::vector<int32_t> out_row = output_rows(P0);
+      quads.resize(kQuadPackings);
+      for (int i = 0; i < kQuadPackings; ++i) {
+        pack_quads(csr.row_ptr, csr.col_idx, csr.values, M, K, kQuadCaps[i], out_row.data(), &quads[i]);
+        total += quad_bytes(quads[i]);
+      }
+    }
     if (total > 0) {
       if (hipMalloc(&plan->d_mem, (size_t)total) != hipSuccess) {
         (void)hipGetLastError();
@@ -974,6 +1010,28 @@ sdnn_status sdnn_plan_create(const int32_t* row_ptr, const int32_t* col_idx, con
         memcpy(host.data() + perm_off, P0.perm.data(), (size_t)M * 4);
         plan->d_perm = (const int32_t*)((char*)plan->d_mem + perm_off);
       }
+      int64_t qoff = quad_off;
+      for (size_t i = 0; i < quads.size(); ++i) {
+        const QuadPacked& Q = quads[i];
+        DevQuads& d = plan->quads[i];
+        auto put = [&](const auto& v) {
+          const void* at = (const char*)plan->d_mem + qoff;
+          const size_t bytes = v.size() * sizeof(v[0]);
+          if (bytes) memcpy(host.data() + qoff, v.data(), bytes);
+          qoff += align256((int64_t)bytes);
+          return at;
+        };
+        d.cap = Q.cap;
+        d.nprogs = Q.nprogs;
+        for (const QuadProgram& P : Q.progs) d.blocks += P.blocks;
+        d.longest = Q.nprogs > 0 ? Q.progs[0].blocks : 0;
+        d.stream = (const uint32_t*)put(Q.stream);
+        d.descs = (const uint32_t*)put(Q.descs);
+        d.progs = (const QuadProgram*)put(Q.progs);
+        d.rows = (const int32_t*)put(Q.rows);
+        d.outs = (const int32_t*)put(Q.outs);
+      }
+      plan->nquads = (int)quads.size();
       if (hipMemcpy(plan->d_mem, host.data(), (size_t)total, hipMemcpyHostToDevice) !=
           hipSuccess) {
         (void)hipGetLastError();

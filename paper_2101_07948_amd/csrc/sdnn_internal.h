@@ -101,6 +101,83 @@ constexpr int kShortPanel = 4, kTallPanel = 12, kMidPanel = 8, kTallestPanel = 1
 constexpr int kDeepPanel = 32;
 constexpr int kMaxPackings = 5;
 
+// ---- row quads (spmm_quad_kernel) --------------------------------------------------------
+// Tile width, rows of B per chunk, chunks in the LDS ring, bytes of a staged B row (one tile
+// wide), and producer waves.
+constexpr int kQuadTileCols = 64;
+constexpr int kQuadChunk = 64, kQuadRing = 8;
+constexpr int kQuadRowBytes = 4 * kQuadTileCols;
+constexpr int kQuadProducers = 4;
+// LDS address of the row of zeros that filler entries read
+constexpr int kQuadZeroRow = kQuadRing * kQuadChunk * kQuadRowBytes;
+// Chunks a block may span at most (quad_window picks by density): a wider window costs less
+// filler but leaves fewer chunks of the ring free for DMAs in flight.
+constexpr int kQuadMaxWindow = kQuadRing - 2;
+constexpr int kQuadUnits = 8;           // quad-steps of a block
+constexpr int kQuadTailBlocks = 8;      // zero blocks after the last program
+constexpr int kQuadLoShift = 6, kQuadHiShift = 19;      // descriptor fields
+constexpr uint32_t kQuadMaxBlocks = 0x3f, kQuadLoMask = 0x1fff;
+constexpr uint32_t kQuadMoreDescs = 1u << kQuadLoShift;  // 64th descriptor: load the next 64
+constexpr int kQuadCaps[] = {1, 2, 4, 8};  // the packings' largest programs, in quads
+constexpr int kQuadPackings = 4, kQuadMaxCap = 8;
+static_assert(kQuadMaxWindow <= kQuadRing, "ring too short");
+
+// Host-side form of W for the row-quad kernel.  Rows, sorted by nonzeros (descending), form
+// programs of NS quads of four rows: the most quads of 1, 2, 4, 8 up to the packing's cap for
+// which the program is no longer than kQuadSlack times cap quads of average rows, so that the
+// programs carry about equal work whatever the rows' lengths (a program is as long as NS times
+// its longest row).  A program's entries are cut into blocks of 8 / NS steps; a step holds
+// one entry of each row, or a filler (weight 0, the row of zeros), each row's entries in
+// ascending column order.  While the program's lowest unread chunk is c, a block takes no
+// entry from chunk c + window or above (a row that far ahead of the program's slowest one gets
+// fillers).  Descriptors (one dword, see kQuadLoShift; a zero dword ends a program, every 64th
+// is kQuadMoreDescs) cover runs of blocks of one lowest chunk that span at most one chunk
+// more than the first of them.  A block is 64 dwords: with NS <= 2, dword 16 r + u is the
+// weight of row r of set u % NS (of four rows) in step u / NS, u < 8, and dword 16 r + 8 + u its
+// LDS address (k % (kQuadRing * kQuadChunk)) * kQuadRowBytes; with NS >= 4, dword 4 r + 2 u is
+// the weight of row r of set u % (NS / 4) (of 16 rows) in step u / (NS / 4), u < 2, and dword
+// 4 r + 2 u + 1 its LDS address.
+inline int quad_dword(int NS, int j, int s) {  // of row j's weight in step s; see above
+  if (NS <= 2) return 16 * (j % 4) + s * NS + j / 4;
+  return 4 * (j % 16) + 2 * (s * (NS / 4) + j / 16);
+}
+inline int quad_addr_at(int NS) { return NS <= 2 ? 8 : 1; }  // the address's dword past it
+struct QuadProgram {
+  int32_t start;  // first block, or -1 (no entries)
+  int32_t desc;   // first descriptor
+  int32_t NS;     // quads
+  int32_t blocks;
+};
+struct QuadPacked {
+  int32_t cap = 0, nprogs = 0;
+  std::vector<QuadProgram> progs;    // [nprogs], longest first
+  std::vector<int32_t> rows;         // [nprogs*cap*4] original row, or -1
+  std::vector<int32_t> outs;         // [nprogs*cap*4] row of C, or -1
+  std::vector<uint32_t> stream;      // [64 * (blocks + kQuadTailBlocks)]
+  std::vector<uint32_t> descs;       // padded with 64 zeros (the wave loads 64 at a time)
+};
+constexpr double kQuadSlack = 1.4;
+
+// Packs W (validated CSR); out_row[i] is the row of C that row i is stored to.
+void pack_quads(const int32_t* row_ptr, const int32_t* col_idx, const float* values, int32_t M,
+                int32_t K, int32_t cap, const int32_t* out_row, QuadPacked* out);
+// Walks the packed form and checks that every entry appears once, in its row, in ascending
+// column order, with unchanged bits, within the window its descriptor states.
+bool check_quads(const int32_t* row_ptr, const int32_t* col_idx, const float* values, int32_t M,
+                 int32_t K, const int32_t* out_row, const QuadPacked& Q);
+
+// One quad packing in device memory.
+struct DevQuads {
+  int32_t cap = 0, nprogs = 0;
+  int64_t blocks = 0;   // of all programs
+  int32_t longest = 0;  // blocks of the longest program
+  const uint32_t* stream = nullptr;
+  const uint32_t* descs = nullptr;
+  const QuadProgram* progs = nullptr;
+  const int32_t* rows = nullptr;
+  const int32_t* outs = nullptr;
+};
+
 // CSR validation; returns SDNN_OK or SDNN_ERR_*.
 sdnn_status validate_csr(const int32_t* row_ptr, const int32_t* col_idx, int32_t M, int32_t K);
 // Algorithm 1 on 64-bit column bitsets (inputs already validated).
@@ -119,11 +196,19 @@ std::vector<uint32_t> narrow_stream(const std::vector<uint32_t>& entries);
 // True if `narrow` is narrow_stream(entries) field by field (decoded independently).
 bool check_narrow_stream(const std::vector<uint32_t>& entries, const std::vector<uint32_t>& narrow);
 
+// Launch of the row-quad kernel: packing (index into sdnn_plan_s::quads), consumer waves.
+struct QuadCfg {
+  int32_t pack = 0, waves = 0;
+};
+
 // A launch shape sdnn_plan_tune measured fastest for one N: which packing, how many
 // consumer waves per workgroup and which tile width; and, for plans with K-segments, the
-// workgroups along K and the tile width of the fastest K-split call (0: not measured).
+// workgroups along K and the tile width of the fastest K-split call (0: not measured).  The
+// panel shape is recorded also where the row-quad kernel was faster.
 struct TunedShape {
   int32_t N = 0, pack = 0, waves = 0, tile = 256, splits = 0, split_tile = 0;
+  int32_t quads = 0;  // the row-quad launch `quad` was faster than the panel shape
+  QuadCfg quad;
 };
 constexpr int kTunedSlots = 8;
 
@@ -161,6 +246,8 @@ struct sdnn_plan_s {
   int32_t tile_cols = 0;       // 0: the launch picks 256 or 128 columns per tile; else fixed
   const int32_t* d_perm = nullptr;  // [M] perm on the device (K-segmented plans only)
   sdnn::DevPacking pk[sdnn::kMaxPackings];
+  int nquads = 0;              // quad packings (default plans: panel_rows = 0, tile_cols = 0)
+  sdnn::DevQuads quads[sdnn::kQuadPackings];
   sdnn::TunedShape tuned[sdnn::kTunedSlots];  // filled by sdnn_plan_tune
   int32_t ntuned = 0;
 };
@@ -197,6 +284,12 @@ void launch_shape(const sdnn_plan_s* p, int32_t N, int32_t* panel_rows, int32_t*
 // and records the fastest in p->tuned.
 hipError_t tune_spmm(sdnn_plan_s* p, const float* B, float* C, int32_t N, hipStream_t stream,
                      TunedShape* chosen);
+// The row-quad kernel (sdnn_quad.hip): whether it serves the plan's calls at N columns, the
+// launch it picks at N, and its launch.
+bool quads_serve(const sdnn_plan_s* p, int32_t N);
+QuadCfg quad_shape(const sdnn_plan_s* p, int32_t N);
+hipError_t launch_quads(const sdnn_plan_s* p, const float* B, float* C, int32_t N,
+                        const float* bias, int epi, const QuadCfg& cfg, hipStream_t stream);
 hipError_t launch_dense(const float* W, const float* B, float* C, int32_t M, int32_t K, int32_t N,
                         const float* bias, int epi, hipStream_t stream);
 }  // namespace sdnn

@@ -41,6 +41,7 @@
 #include <mutex>
 #include <vector>
 
+#include "sdnn_device.h"
 #include "sdnn_internal.h"
 
 namespace sdnn {
@@ -147,48 +148,6 @@ constexpr int kCtlWords = 256;
 static_assert(512 + 16 * kProducers <= kCtlWords * 4, "filler words outside the control area");
 static_assert(kAsmProducersN <= kProducers, "ready words overlap the progress words");
 static_assert(kProducers <= 16, "ready words overlap the progress words");
-
-// GELU(x) = x Phi(x) = 0.5 x (1 + erf(x / sqrt 2)) (the exact erf form).  erf(z) for
-// z >= 0 comes from Abramowitz & Stegun 7.1.26 (Hastings' approximation, absolute error
-// at most 1.5e-7): erf(z) = 1 - q, q = t (a1 + t (a2 + t (a3 + t (a4 + t a5)))) e^(-z^2),
-// t = 1 / (1 + p z); with erf(-z) = -erf(z), GELU(x) = 0.5 x (2 - q) for x >= 0 and
-// 0.5 x q for x < 0 (no cancellation on the negative side).  The reciprocal and the
-// exponential are the hardware's (v_rcp_f32, v_exp_f32, about 1 ulp); the result is within
-// 0.5 |x| * 4e-7 of the exact GELU, far inside the 1e-6 floor of the parity bar at the
-// |x| these layers reach, and costs about a third of the library erff's instructions.
-__device__ __forceinline__ float gelu(float x) {
-  const float z = fabsf(x) * 0.70710678118654752f;
-  const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f, z, 1.0f));
-  float poly = fmaf(t, 1.061405429f, -1.453152027f);
-  poly = fmaf(t, poly, 1.421413741f);
-  poly = fmaf(t, poly, -0.284496736f);
-  poly = fmaf(t, poly, 0.254829592f);
-  poly *= t;
-  const float q = poly * __builtin_amdgcn_exp2f(-z * z * 1.4426950408889634f);
-  return 0.5f * x * (x >= 0.0f ? 2.0f - q : q);
-}
-
-// C is written once and not read again by the kernel: its stores are non-temporal, so the
-// output stream does not evict the B tiles and the packed stream from L2 (the stores of the
-// 201 MB output of the 3072 x 768 layer at N = 16384 otherwise push the 0.57 MB stream out
-// between tiles).
-typedef float nt_float4 __attribute__((ext_vector_type(4)));
-typedef float nt_float2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ void store_c4(float* p, float x, float y, float z, float w) {
-  const nt_float4 v = {x, y, z, w};
-  __builtin_nontemporal_store(v, reinterpret_cast<nt_float4*>(p));
-}
-__device__ __forceinline__ void store_c2(float* p, float x, float y) {
-  const nt_float2 v = {x, y};
-  __builtin_nontemporal_store(v, reinterpret_cast<nt_float2*>(p));
-}
-__device__ __forceinline__ void store_c1(float* p, float x) { __builtin_nontemporal_store(x, p); }
-
-__device__ __forceinline__ float activation(float x, int epi) {
-  if (epi == SDNN_EPI_RELU) return fmaxf(x, 0.0f);
-  if (epi == SDNN_EPI_GELU) return gelu(x);
-  return x;
-}
 
 // Scalar launch parameters (the pointers are separate __restrict__ kernel arguments so
 // the compiler may read them through the scalar cache).
@@ -915,12 +874,20 @@ void launch_shape(const sdnn_plan_s* p, int32_t N, int32_t* panel_rows, int32_t*
 
 hipError_t launch_spmm(const sdnn_plan_s* p, const float* B, float* C, int32_t N,
                        const float* bias, int epi, hipStream_t stream) {
+  if (quads_serve(p, N)) {
+    const TunedShape* t = nullptr;
+    for (int i = 0; i < p->ntuned; ++i)
+      if (p->tuned[i].N == N) t = &p->tuned[i];
+    if (!t || t->quads)
+      return launch_quads(p, B, C, N, bias, epi, t ? t->quad : quad_shape(p, N), stream);
+  }
   return launch_panels(p, B, C, N, bias, epi, nullptr, nullptr, nullptr, 0, stream);
 }
 
 hipError_t launch_spmm_split(const sdnn_plan_s* p, const float* B, float* C, int32_t N,
                              const float* bias, int epi, int splits, float* ws,
                              hipStream_t stream) {
+  if (split_runs_of(p, N, splits, false, nullptr) == 1) return launch_spmm(p, B, C, N, bias, epi, stream);
   return launch_panels(p, B, C, N, bias, epi, nullptr, nullptr, ws, splits, stream);
 }
 
@@ -974,6 +941,34 @@ hipError_t tune_spmm(sdnn_plan_s* p, const float* B, float* C, int32_t N, hipStr
       best = ms_best[i];
       *chosen = cands[i];
     }
+  // the row-quad kernel, where it serves the call: every packing with its most consumer waves
+  // and three smaller counts, and the cost model's choice
+  if (err == hipSuccess && quads_serve(p, N)) {
+    std::vector<QuadCfg> quads{quad_shape(p, N)};
+    for (int k = 0; k < p->nquads; ++k)
+      for (int w : {12, 9, 6, 3})
+        if (w <= std::max(3, p->quads[k].nprogs)) quads.push_back(QuadCfg{k, w});
+    std::vector<float> ms_quad(quads.size(), -1.0f);
+    for (int pass = 0; pass < 2; ++pass)
+      for (size_t i = 0; i < quads.size() && err == hipSuccess; ++i) {
+        for (int r = 0; r < 2 && err == hipSuccess; ++r)
+          err = launch_quads(p, B, C, N, nullptr, 0, quads[i], stream);
+        if (err == hipSuccess) err = hipEventRecord(e0, stream);
+        for (int r = 0; r < 8 && err == hipSuccess; ++r)
+          err = launch_quads(p, B, C, N, nullptr, 0, quads[i], stream);
+        if (err == hipSuccess) err = hipEventRecord(e1, stream);
+        if (err == hipSuccess) err = hipEventSynchronize(e1);
+        float ms = 0.0f;
+        if (err == hipSuccess) err = hipEventElapsedTime(&ms, e0, e1);
+        if (err == hipSuccess && (ms_quad[i] < 0.0f || ms < ms_quad[i])) ms_quad[i] = ms;
+      }
+    for (size_t i = 0; i < quads.size() && err == hipSuccess; ++i)
+      if (ms_quad[i] <= best) {
+        best = ms_quad[i];
+        chosen->quads = 1;
+        chosen->quad = quads[i];
+      }
+  }
   int slot = -1;
   if (err == hipSuccess) {
     for (int i = 0; i < p->ntuned; ++i)

@@ -1,0 +1,483 @@
+// gfx950 row-quad kernel of the sparse-weight x dense-activation product (SparseDNN, arXiv
+// 2101.07948, Sec. 3.2.2): the kernel that calls on a default plan run on.
+//
+//   * A consumer wavefront holds a program of 4, 8, 16 or 32 rows of W over a tile of 64
+//     columns of C.  Its lanes form groups of 16 (programs of 4 and 8 rows) or 4 (16 and 32
+//     rows), a group per row of a set; one step multiplies one entry of each group's row, so
+//     one ds_read_b128 reads four or sixteen different B rows, and an entry's weight and LDS
+//     address reach its group by a DPP broadcast (gen_quad_asm.py).  The accumulators are
+//     plain registers: no VGPR index mode, no scalar weights.
+//   * Against a wave per panel of rows and 256 columns (spmm_panel_kernel), a workgroup's
+//     tile is a quarter as wide for the same outputs, so it stages a quarter of the bytes of
+//     B per output, and the LDS ring holds 512 rows of B instead of 128.
+//   * Rows of about equal length share a program, and a program has the height that makes it
+//     about as long as the others of its packing, so the waves of a workgroup, which the ring
+//     couples to within 512 rows of B, carry equal work.
+//   * B is staged by four producer wavefronts with direct global->LDS DMA, four 256-byte rows
+//     per instruction, through a ring of kQuadRing chunks of kQuadChunk rows; producers and
+//     consumers synchronise through LDS words as in spmm_panel_kernel (chunks landed; lowest
+//     chunk a consumer still reads), every wait bounded by a poll budget.
+//   * Each row sums its entries in ascending column order with fused multiply-adds, as in
+//     every kernel of the library, so C is the same bit for bit.
+//
+// What bounds it: LDS.  Every entry reads 16 bytes of B per four columns, 1 KB per quad-step
+// (four entries x 64 columns), 4.05 cycles of a CU's LDS; the FMAs, address and weight ops of a
+// quad-step take 16.4 cycles of a SIMD (a quarter of the CU) in groups of 4 lanes and 22.7 in
+// groups of 16, so the groups of 4 run at LDS's pace (the 768 x 3072 layer at 90 %, N = 4096:
+// LDS active in 76 % of the kernel's cycles, no bank conflicts) and are taken where a workgroup
+// has rows enough to fill its waves with them.  Measured against the panel kernel: that layer
+// 66.4 -> 47.3 us, 768 x 768 at 90 %, N = 1024 13.6 -> 8.4 us, 2048 x 2048 at 70 %, N = 512
+// 56.0 -> 36.2 us, 3072 x 768 at 97 %, N = 16384 with GELU 124.2 -> 108.6 us.
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+#include <stdlib.h>
+
+#include <algorithm>
+
+#include "sdnn_device.h"
+#include "sdnn_internal.h"
+
+namespace sdnn {
+namespace {
+
+template <int N>
+using group_acc_t = float __attribute__((ext_vector_type(N)));
+
+struct QuadConsumer {
+  const uint32_t* stream;  // the program's first block
+  const uint32_t* descs;   // its descriptors
+  uint32_t vlane;          // 16 * (lane % 16): the lane's byte offset in a staged B row
+  uint32_t lane4;          // 4 * lane
+  uint32_t prog_addr;      // LDS address of this consumer's progress word
+  uint32_t ready_addr;     // LDS address of the ready words
+  uint32_t overrun_addr;   // LDS address of the workgroup's overrun word
+  uint32_t poll_budget;    // failed readiness checks the wave may poll through in total
+  uint32_t chunk_base;     // ring chunk number of the item's chunk 0
+  uint32_t next_progress;  // progress word written when the program is done
+};
+
+#include "quad_asm_gen.h"
+static_assert(kQuadAsmTailBlocks <= kQuadTailBlocks, "stream tail shorter than the prefetch");
+static_assert(kQuadAsmUnits == kQuadUnits, "block layout mismatch");
+static_assert(kQuadAsmLoShift == kQuadLoShift && kQuadAsmHiShift == kQuadHiShift &&
+                  kQuadAsmCountMask == kQuadMaxBlocks,
+              "descriptor fields mismatch");
+
+constexpr uint32_t kProgressEnd = 0x7fffffffu;
+constexpr int kPollBudgetQuad = 1 << 22;
+// LDS: the ring, a row of zeros (read by the filler entries), then the control words:
+// ready[4] at +0, progress[16] at +64, the overrun word at +128.
+constexpr int kRingB = kQuadRing * kQuadChunk * kQuadRowBytes;
+constexpr int kCtl = kRingB + kQuadRowBytes;
+constexpr int kLdsBytes = kCtl + 256;
+static_assert(kQuadZeroRow == kRingB, "the filler entries' row of zeros follows the ring");
+constexpr int kMaxQuadConsumers = 16 - kQuadProducers;
+
+struct QuadArgs {
+  int32_t K, N, nchunks, nprogs;
+  int32_t ring_chunks;  // nchunks rounded up to the ring: chunk numbers an item takes up
+  int32_t n_rb, n_tiles, total_wg, per_xcd, epi;
+  uint32_t poll_budget;
+};
+
+// Staging kinds: 16-byte pieces and stores (N % 4 == 0, B and C 16-byte aligned) or 4-byte ones
+// (any N).
+enum { kQuadVec = 0, kQuadDword = 1 };
+
+// ---- producers --------------------------------------------------------------------------
+// (M0, the DMAs' LDS address, is not a register the compiler allocates; nothing else in these
+// kernels uses it)
+
+template <int BYTES>
+__device__ __forceinline__ void dma_saddr(uint32_t lds, uint32_t voff, uint64_t base) {
+  if constexpr (BYTES == 16)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                 :: "s"(lds), "v"(voff), "s"(base) : "memory");
+  else
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
+                 :: "s"(lds), "v"(voff), "s"(base) : "memory");
+}
+// The four 1 KB DMAs of a producer's rows of a full chunk under one M0: the instruction
+// offset (13 bits, signed) moves the global and the LDS address alike, so DMA j carries
+// offset 1024 j, and voff[j] = the lane's offset - 1024 j + 4096 from base - 4096.
+__device__ __forceinline__ void dma_rows(uint32_t lds, const uint32_t (&v)[4], uint64_t base) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+               "global_load_lds_dwordx4 %1, %5\n\t"
+               "global_load_lds_dwordx4 %2, %5 offset:1024\n\t"
+               "global_load_lds_dwordx4 %3, %5 offset:2048\n\t"
+               "global_load_lds_dwordx4 %4, %5 offset:3072"
+               :: "s"(lds), "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "s"(base - 4096)
+               : "memory");
+}
+__device__ __forceinline__ void dma_vaddr(uint32_t lds, uint64_t addr) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+               :: "s"(lds), "v"(addr) : "memory");
+}
+__device__ __forceinline__ void lds_write(uint32_t addr, uint32_t v) {
+  asm volatile("ds_write_b32 %0, %1" :: "v"(addr), "v"(v) : "memory");
+}
+// min of the 16 progress words (the slots of absent consumers hold kProgressEnd)
+__device__ __forceinline__ uint32_t min_progress(uint32_t addr) {
+  typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+  u4 a, b, c, d;
+  asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %4 offset:16\n\t"
+               "ds_read_b128 %2, %4 offset:32\n\tds_read_b128 %3, %4 offset:48\n\t"
+               "s_waitcnt lgkmcnt(0)"
+               : "=&v"(a), "=&v"(b), "=&v"(c), "=&v"(d) : "v"(addr) : "memory");
+  uint32_t m = kProgressEnd;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) m = min(m, min(min(a[i], b[i]), min(c[i], d[i])));
+  return __builtin_amdgcn_readfirstlane(m);
+}
+// Stages rows [r0, r0 + kQuadChunk) of the tile at columns n0.. into the ring slot at LDS
+// address `lds`: 16-byte pieces, four rows per DMA (lane group r: row r), or 4-byte pieces, a
+// row per DMA.  Rows past K stage row K-1 again (no entry reads them); lanes past N stay out.
+// Always kLoads<STAGE> DMAs.
+template <int STAGE>
+constexpr int kLoads = STAGE == kQuadDword ? kQuadChunk : kQuadChunk / 4;
+
+template <int STAGE>
+__device__ __forceinline__ void stage_chunk(const QuadArgs& a, const float* B, int n0, int r0,
+                                            uint32_t lds, const uint32_t (&voff)[4], int lane) {
+  const uint32_t row_bytes = (uint32_t)a.N * 4u;
+  const uint64_t tile = (uint64_t)(uintptr_t)(B + n0);
+  const uint32_t lrow = (uint32_t)lane >> 4, lcol = (uint32_t)(lane & 15) * 16u;
+  if constexpr (STAGE == kQuadVec) {
+    if (n0 + 4 * (lane & 15) < a.N) {
+      if (r0 + kQuadChunk <= a.K) {
+        uint64_t base = tile + (uint64_t)(uint32_t)r0 * row_bytes;
+#pragma unroll
+        for (int j = 0; j < kQuadChunk / 16; ++j, base += 16ull * row_bytes)
+          dma_rows(lds + 4096u * j, voff, base);
+      } else {
+#pragma unroll
+        for (int j = 0; j < kQuadChunk / 4; ++j) {
+          const uint32_t row = (uint32_t)min(r0 + 4 * j + (int)lrow, a.K - 1);
+          dma_vaddr(lds + 1024u * j, tile + (uint64_t)row * row_bytes + lcol);
+        }
+      }
+    }
+  } else {
+    if (n0 + lane < a.N) {
+#pragma unroll 8
+      for (int j = 0; j < kQuadChunk; ++j) {
+        const uint32_t row = (uint32_t)min(r0 + j, a.K - 1);
+        dma_saddr<4>(lds + (uint32_t)j * kQuadRowBytes, 4u * (uint32_t)lane,
+                     tile + (uint64_t)row * row_bytes);
+      }
+    }
+  }
+}
+
+// Producer `prod` stages every kQuadProducers-th chunk, whole: chunk g goes to ring slot
+// g % kQuadRing once g < min(progress) + kQuadRing.  (A chunk split between the producers
+// would cost each of them the loop's 700 cycles of scalar work per chunk; so, that cost is
+// paid once per kQuadProducers chunks.)  Its ready word is the next chunk it has not landed,
+// so every chunk below the smallest ready word has landed.  Two chunks are in flight: a
+// chunk's DMAs go out before the previous one's are waited for.  An item takes ring_chunks
+// chunk numbers; those past nchunks hold no rows (an item's chunk c keeps ring slot
+// c % kQuadRing).
+template <int STAGE>
+__device__ __forceinline__ void produce(const float* B, const QuadArgs& a, int prod, int lane, int item,
+                        int nitems) {
+  constexpr int L = kLoads<STAGE>;
+  static_assert(L <= 32 || STAGE == kQuadDword, "vmcnt field");
+  const uint32_t ready = kCtl + 4u * prod, prog0 = kCtl + 64, overrun = kCtl + 128;
+  const uint32_t row_bytes = (uint32_t)a.N * 4u;
+  const uint32_t total = (uint32_t)nitems * (uint32_t)a.ring_chunks;
+  uint32_t limit = kQuadRing, budget = a.poll_budget;
+  bool pending = false;  // the previous chunk has DMAs in flight
+  int ci = prod;         // chunk within the item
+  int n0 = item / a.n_rb * kQuadTileCols;
+  uint32_t voff[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    voff[j] = (uint32_t)(lane & 15) * 16u + (((uint32_t)lane >> 4) + 4u * j) * row_bytes - 1024u * j + 4096u;
+  for (uint32_t g = (uint32_t)prod; g < total; g += kQuadProducers) {
+    if (g >= limit) {
+      limit = min_progress(prog0) + kQuadRing;
+      if (g >= limit) {
+        if (pending) {  // nothing to stage: land the previous chunk
+          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+          if (lane == 0) lds_write(ready, g);
+          pending = false;
+        }
+        while ((limit = min_progress(prog0) + kQuadRing) <= g) {
+          if (budget == 0) {
+            // budget spent: stage anyway, after saying that a slot still being read may go
+            lds_write(overrun, 1u);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            break;
+          }
+          --budget;
+          __builtin_amdgcn_s_sleep(1);
+        }
+      }
+    }
+    const bool real = ci < a.nchunks;
+    const uint32_t slot = (g % kQuadRing) * (kQuadChunk * kQuadRowBytes);
+    if (real) stage_chunk<STAGE>(a, B, n0, ci * kQuadChunk, slot, voff, lane);
+    if (pending) {  // the previous chunk has landed once at most this one's DMAs are left
+      if (real) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(L <= 63 ? L : 0) : "memory");
+      else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      if (lane == 0) lds_write(ready, g);
+      pending = false;
+    }
+    if (real && STAGE != kQuadDword) {
+      pending = true;
+    } else {  // no rows, or 64 DMAs (the counter's range): land at once
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      if (lane == 0) lds_write(ready, g + kQuadProducers);
+    }
+    ci += kQuadProducers;
+    if (ci >= a.ring_chunks) {  // the next item
+      ci -= a.ring_chunks;
+      item += a.total_wg;
+      n0 = item / a.n_rb * kQuadTileCols;
+    }
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  if (lane == 0) lds_write(ready, kProgressEnd);
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+}
+
+// ---- kernel -----------------------------------------------------------------------------
+
+// One program of a consumer wave: its loop, then the epilogue of its 4 NS rows.  Lane group g
+// of set q holds row q * kRows + g, the lane kVecs times four columns.
+template <int NS, int STAGE>
+__device__ __forceinline__ void run_program(QuadConsumer& ca, bool entries, const int32_t* rows,
+                                            const int32_t* outs, float* C, const float* bias, int n0,
+                                            int lane, const QuadArgs& a) {
+  constexpr int kGroup = NS <= 2 ? 16 : 4, kRows = 64 / kGroup, kSets = 4 * NS / kRows;
+  constexpr int kVecs = kQuadTileCols / (4 * kGroup);
+  const int quarter = lane / kGroup % 4;  // group g's i-th vector is quarter i ^ (g % 4)
+  int out[kSets];
+  float bb[kSets];
+#pragma unroll
+  for (int q = 0; q < kSets; ++q) {
+    const int j = q * kRows + lane / kGroup;
+    out[q] = outs[j];
+    const int src = rows[j];
+    bb[q] = bias && src >= 0 ? bias[src] : 0.0f;
+  }
+  group_acc_t<4 * kVecs> acc[kSets];
+#pragma unroll
+  for (int q = 0; q < kSets; ++q)
+#pragma unroll
+    for (int k = 0; k < 4 * kVecs; ++k) acc[q][k] = 0.0f;
+  if (entries) {
+    ca.vlane = (uint32_t)(lane % kGroup) * 16u + (kVecs > 1 ? (uint32_t)quarter * 64u : 0u);
+    if constexpr (NS == 1) consume_quads1(acc, ca);
+    if constexpr (NS == 2) consume_quads2(acc, ca);
+    if constexpr (NS == 4) consume_quads4(acc, ca);
+    if constexpr (NS == 8) consume_quads8(acc, ca);
+  }
+#pragma unroll
+  for (int q = 0; q < kSets; ++q) {
+    if (out[q] < 0) continue;
+    float* c = C + (size_t)out[q] * a.N;
+#pragma unroll
+    for (int i = 0; i < kVecs; ++i) {
+      const int n = n0 + 4 * (lane % kGroup) + 4 * kGroup * (kVecs > 1 ? i ^ quarter : 0);
+      float v[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] = activation(acc[q][4 * i + k] + bb[q], a.epi);
+      if (STAGE != kQuadDword) {
+        if (n < a.N) store_c4(c + n, v[0], v[1], v[2], v[3]);
+      } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          if (n + k < a.N) store_c1(c + n + k, v[k]);
+      }
+    }
+  }
+}
+
+// STAGE: 16-byte staging and stores (N % 4 == 0, B and C 16-byte aligned) or 4-byte ones;
+// CAP: the packing's largest programs, in quads.  blockDim.x = 64 * (consumers +
+// kQuadProducers).  A workgroup takes the items (tile, row-block) numbered w, w + total_wg, ...
+// in tile-major order; the consecutive workgroups of one XCD work on consecutive items and
+// share their tiles' B rows in its L2.  Consumer w of a row-block takes the programs of one
+// stratum of the list sorted by length, in snake order over the row-blocks, so that
+// row-blocks carry equal work, and the strata go to the SIMDs (wave w runs on SIMD w % 4)
+// in snake order too.
+template <int CAP, int STAGE>
+__global__ __launch_bounds__(1024) void spmm_quad_kernel(
+    const uint32_t* __restrict__ stream, const uint32_t* __restrict__ descs,
+    const QuadProgram* __restrict__ progs, const int32_t* __restrict__ rows,
+    const int32_t* __restrict__ outs, const float* __restrict__ B, float* __restrict__ C,
+    const float* __restrict__ bias, QuadArgs a) {
+  // the loops form LDS addresses from the stream alone: the ring starts at LDS 0, which
+  // holds because this is the kernel's only LDS object
+  __shared__ __attribute__((aligned(16))) uint32_t lds[kLdsBytes / 4];
+  const int bid = blockIdx.x;
+  const int lin = (bid & 7) * a.per_xcd + (bid >> 3);
+  if (lin >= a.total_wg) return;  // whole workgroup leaves before the barrier
+  const int nc = (int)(blockDim.x >> 6) - kQuadProducers;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  const int prod = wave - nc;
+  const int items = a.n_tiles * a.n_rb;
+  const int nitems = (items - lin + a.total_wg - 1) / a.total_wg;
+
+  // LDS is read and written by assembly alone, at addresses from 0 up; handing the object's
+  // address to an asm statement keeps it (and its size) in the kernel
+  const uint32_t lds_base = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) uint32_t*)lds);
+  asm volatile("" ::"v"(lds_base) : "memory");
+  const uint32_t progress = kCtl + 64u + 4u * (uint32_t)wave;
+  if (prod >= 0) {
+    if (lane == 0) lds_write(kCtl + 4u * prod, (uint32_t)prod);                    // nothing landed
+    if (prod == 0 && lane >= nc && lane < 16) lds_write(kCtl + 64u + 4u * lane, kProgressEnd);  // absent
+    if (prod == 0 && lane == 0) lds_write(kCtl + 128u, 0u);                        // no overrun
+    if (prod == 1) lds_write(kRingB + 4u * lane, 0u);                              // the row of zeros
+  } else if (lane == 0) {
+    lds_write(progress, 0u);
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __syncthreads();
+
+  if (prod >= 0) {
+    produce<STAGE>(B, a, prod, lane, lin, nitems);
+    return;
+  }
+
+  const int g4 = wave >> 2, i4 = wave & 3;
+  const int stratum = (g4 & 1) && 4 * g4 + 4 <= nc ? 4 * g4 + 3 - i4 : wave;
+  for (int it = 0; it < nitems; ++it) {
+    const int item = lin + it * a.total_wg;
+    const int tile = item / a.n_rb, rb = item - tile * a.n_rb;
+    const uint32_t cbase = (uint32_t)(it * a.ring_chunks);
+    const uint32_t next = it + 1 < nitems ? (uint32_t)((it + 1) * a.ring_chunks) : kProgressEnd;
+    const int prog = stratum * a.n_rb + ((stratum & 1) ? a.n_rb - 1 - rb : rb);
+    if (prog >= a.nprogs) {
+      if (lane == 0) lds_write(progress, next);
+      continue;
+    }
+    const QuadProgram P = progs[prog];
+    QuadConsumer ca;
+    ca.stream = stream + (size_t)P.start * 64;
+    ca.descs = descs + P.desc;
+    ca.lane4 = (uint32_t)lane * 4u;
+    ca.prog_addr = progress;
+    ca.ready_addr = kCtl;
+    ca.overrun_addr = kCtl + 128u;
+    ca.poll_budget = a.poll_budget;
+    ca.chunk_base = cbase;
+    ca.next_progress = next;
+    const int at = prog * (4 * CAP);
+    const int n0 = tile * kQuadTileCols;
+    if (P.start < 0 && lane == 0) lds_write(progress, next);  // no entries: only epi(bias)
+    if (CAP == 8 && P.NS == 8) run_program<8, STAGE>(ca, P.start >= 0, rows + at, outs + at, C, bias, n0, lane, a);
+    else if (CAP >= 4 && P.NS == 4) run_program<4, STAGE>(ca, P.start >= 0, rows + at, outs + at, C, bias, n0, lane, a);
+    else if (CAP >= 2 && P.NS == 2) run_program<2, STAGE>(ca, P.start >= 0, rows + at, outs + at, C, bias, n0, lane, a);
+    else run_program<1, STAGE>(ca, P.start >= 0, rows + at, outs + at, C, bias, n0, lane, a);
+  }
+}
+
+template <int CAP, int STAGE>
+hipError_t launch_cap(const DevQuads& d, const float* B, float* C, const float* bias,
+                      const QuadArgs& args, int waves, int grid, hipStream_t stream) {
+  hipLaunchKernelGGL((spmm_quad_kernel<CAP, STAGE>), dim3(grid), dim3(64 * (waves + kQuadProducers)),
+                     0, stream, d.stream, d.descs, d.progs, d.rows, d.outs, B, C, bias, args);
+  return hipGetLastError();
+}
+
+template <int STAGE>
+hipError_t launch_stage(const DevQuads& d, const float* B, float* C, const float* bias,
+                        const QuadArgs& args, int waves, int grid, hipStream_t stream) {
+  switch (d.cap) {
+    case 1: return launch_cap<1, STAGE>(d, B, C, bias, args, waves, grid, stream);
+    case 2: return launch_cap<2, STAGE>(d, B, C, bias, args, waves, grid, stream);
+    case 4: return launch_cap<4, STAGE>(d, B, C, bias, args, waves, grid, stream);
+    case 8: return launch_cap<8, STAGE>(d, B, C, bias, args, waves, grid, stream);
+  }
+  return hipErrorInvalidValue;
+}
+
+int env_or(const char* name, int dflt) {
+  const char* s = getenv(name);
+  return s ? atoi(s) : dflt;
+}
+
+// The packing and the consumer waves of a call: those that a cost model gives the least
+// time.  In microseconds, for a workgroup's item (all measured on MI355X):
+//     lat * (longest + mean program)/2 + thr * mean * max(waves / 4, 1)   blocks of 8 quad-steps
+//   + sync * chunks + 0.104 * ring chunks                                 handshakes, staging
+//   + store * rows                                                        epilogue
+// times the rounds of items over the CUs.  lat, thr, sync: 0.085, 0.036, 0.107 for programs
+// of 4 and 8 rows, 0.127, 0.011, 0.080 for those of 16 and 32; store: 0.0057, and 0.0083 for
+// 32-row programs.  Fitted to 4300 timings over 112 problems (M, K = 100 to 3072, 3 to 30 %
+// dense, N = 32 to 16384, uniform and lognormal rows): 10 % rms error, and the pick's time is
+// within 1.7 % of the fastest of the 44 candidates on average (22 % at worst, a 1500 x 100
+// layer at N = 16384).
+QuadCfg choose_quads(const sdnn_plan_s* p, int N) {
+  const int64_t tiles = (N + kQuadTileCols - 1) / kQuadTileCols;
+  const int64_t cus = p->num_cus > 0 ? p->num_cus : 256;
+  const int chunks = (p->K + kQuadChunk - 1) / kQuadChunk;
+  QuadCfg best{0, 1};
+  double best_t = -1.0;
+  for (int i = 0; i < p->nquads; ++i) {
+    const DevQuads& d = p->quads[i];
+    const bool hex = d.cap >= 4;
+    const double mean = (double)d.blocks / d.nprogs;
+    const double lat = (hex ? 0.127 : 0.085) * 0.5 * (mean + d.longest) + (hex ? 0.080 : 0.107) * chunks;
+    for (int w = std::min(2, d.nprogs); w <= std::min(kMaxQuadConsumers, d.nprogs); ++w) {
+      const int64_t items = tiles * ((d.nprogs + w - 1) / w), rounds = (items + cus - 1) / cus;
+      const int staged = rounds > 1 ? (chunks + kQuadRing - 1) / kQuadRing * kQuadRing : chunks;
+      const double t = rounds * (lat + (hex ? 0.011 : 0.036) * mean * std::max(0.25 * w, 1.0) +
+                                 0.104 * staged + (d.cap == 8 ? 0.0083 : 0.0057) * 4.0 * d.cap * w);
+      if (best_t < 0.0 || t < best_t) {
+        best_t = t;
+        best = QuadCfg{i, w};
+      }
+    }
+  }
+  return best;
+}
+
+}  // namespace
+
+// Calls under the panel kernel's test overrides run on it.
+bool quads_serve(const sdnn_plan_s* p, int32_t N) {
+  return p->nquads > 0 && p->K > 0 && (uint64_t)N * 4u * 16 < ((uint64_t)1 << 31) &&
+         !getenv("SDNN_FORCE_WAVES") && !getenv("SDNN_FORCE_WG_PER_TILE") &&
+         !getenv("SDNN_FORCE_TILE_MAJOR_WGS");
+}
+
+QuadCfg quad_shape(const sdnn_plan_s* p, int32_t N) {
+  QuadCfg c = choose_quads(p, N);
+  const int cap = env_or("SDNN_FORCE_QUAD_CAP", 0), waves = env_or("SDNN_FORCE_QUAD_WAVES", 0);  // tests
+  for (int i = 0; i < p->nquads; ++i)
+    if (p->quads[i].cap == cap) c.pack = i;
+  if (waves > 0) c.waves = waves;
+  return c;
+}
+
+hipError_t launch_quads(const sdnn_plan_s* p, const float* B, float* C, int32_t N,
+                        const float* bias, int epi, const QuadCfg& cfg, hipStream_t stream) {
+  const DevQuads& d = p->quads[cfg.pack];
+  const int64_t cus = p->num_cus > 0 ? p->num_cus : 256;
+  const int waves = std::max(1, std::min({cfg.waves, kMaxQuadConsumers, d.nprogs}));
+  QuadArgs args;
+  args.K = p->K;
+  args.N = N;
+  args.nchunks = (p->K + kQuadChunk - 1) / kQuadChunk;
+  args.ring_chunks = (args.nchunks + kQuadRing - 1) / kQuadRing * kQuadRing;
+  args.nprogs = d.nprogs;
+  args.n_rb = (d.nprogs + waves - 1) / waves;
+  args.n_tiles = (N + kQuadTileCols - 1) / kQuadTileCols;
+  args.epi = epi;
+  const int64_t items = (int64_t)args.n_rb * args.n_tiles;
+  if (items > (int64_t)1 << 30) return hipErrorInvalidValue;
+  args.total_wg = (int32_t)std::min(items, cus);
+  args.per_xcd = (args.total_wg + 7) / 8;
+  const int budget = env_or("SDNN_POLL_BUDGET", kPollBudgetQuad);
+  args.poll_budget = budget > 0 ? (uint32_t)budget : 0u;
+  const int grid = args.per_xcd * 8;
+  const bool vec = N % 4 == 0 && (((uintptr_t)B | (uintptr_t)C) & 15) == 0;
+  return vec ? launch_stage<kQuadVec>(d, B, C, bias, args, waves, grid, stream)
+             : launch_stage<kQuadDword>(d, B, C, bias, args, waves, grid, stream);
+}
+
+}  // namespace sdnn

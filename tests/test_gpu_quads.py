@@ -1,0 +1,139 @@
+"""GPU parity of the row-quad kernel (the kernel of default plans) at the edges of its tiles,
+programs and ring, against the CPU oracle with the parity bar, and bit for bit against the
+panel kernel (a plan of 4-row panels): both sum each row's entries in ascending column order
+with fused multiply-adds."""
+import os
+
+import numpy as np
+import pytest
+
+import oracle
+import paper_2101_07948_amd as sd
+from conftest import tol_fp32
+from paper_2101_07948_amd import inputs
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.fixture
+def force():
+    """Sets the kernel's launch overrides for one test."""
+    keys = ("SDNN_FORCE_QUAD_CAP", "SDNN_FORCE_QUAD_WAVES")
+    old = {k: os.environ.get(k) for k in keys}
+
+    def set_(cap, waves):
+        os.environ.update({keys[0]: str(cap), keys[1]: str(waves)})
+    yield set_
+    for k, v in old.items():
+        if v is None:
+            os.environ.pop(k, None)
+        else:
+            os.environ[k] = v
+
+
+def run(plan, Bt, bias, epi):
+    bt = None if bias is None else torch.from_numpy(np.ascontiguousarray(bias)).to(DEV)
+    C = torch.full((plan.M, Bt.shape[1]), float("nan"), device=DEV)
+    plan.spmm(Bt, C, bt, epi)
+    torch.cuda.synchronize()
+    return C.cpu().numpy()
+
+
+def check(W, N, label, epi="none", bias=True, offset=0, **kw):
+    print(f"quads: {label} N={N}", flush=True)
+    B = inputs.dense_B(W.K, N, inputs.CFG_TEST, 7000 + N)
+    b = inputs.bias_normal(W.M, inputs.CFG_TEST, 7001, 0.02) if bias else None
+    flat = torch.empty(W.K * N + 4, device=DEV)
+    Bt = flat[offset:offset + W.K * N].view(W.K, N)
+    Bt.copy_(torch.from_numpy(B))
+    with sd.Plan.from_csr(W, **kw) as plan:
+        got, perm = run(plan, Bt, b, epi), plan.perm
+    with sd.Plan.from_csr(W, panel_rows=4, **kw) as plan:
+        panel = run(plan, Bt, b, epi)
+    ref, bound = oracle.spmm_f64(W.row_ptr, W.col_idx, W.values, W.K, B, b, epi)
+    if kw.get("out_permuted"):
+        ref, bound = ref[perm], bound[perm]
+    err = np.abs(got.astype(np.float64) - ref)
+    assert (err <= tol_fp32(bound, epi)).all(), label
+    assert np.array_equal(got, panel), label
+
+
+@pytest.mark.parametrize("cap", [1, 2, 4, 8])
+@pytest.mark.parametrize("M,K,N", [
+    (1, 1, 1), (3, 63, 4), (4, 64, 64), (33, 65, 68), (50, 300, 63),   # tile and chunk remainders
+    (130, 512, 132), (130, 513, 130), (200, 1100, 65),                  # the ring's 512 rows, and past
+])
+def test_program_heights(force, cap, M, K, N):
+    """Programs of up to 4, 8, 16 and 32 rows over one and several tiles, 16- and 4-byte
+    staging, rows past M, K inside one chunk, exactly the ring and wrapping it."""
+    force(cap, 3)
+    W = inputs.pattern_uniform(M, K, 0.2, inputs.CFG_TEST, 7100 + M + K, 0.05)
+    check(W, N, f"cap {cap} M {M} K {K}", "relu")
+
+
+@pytest.mark.parametrize("cap,waves", [(1, 1), (2, 12), (4, 5), (8, 12)])
+def test_row_length_mix(force, cap, waves):
+    """Lognormal rows with a few full and many empty ones: programs of every height in one
+    launch, programs without entries, GELU, permuted output."""
+    force(cap, waves)
+    rng = np.random.default_rng(7200)
+    M, K = 500, 900
+    lens = np.minimum(K, (30 * np.exp(rng.normal(0, 1.2, M))).astype(int))
+    lens[:3], lens[100:220] = K, 0
+    cols = [np.sort(rng.choice(K, n, replace=False)) for n in lens]
+    row_ptr = np.zeros(M + 1, dtype=np.int32)
+    np.cumsum(lens, out=row_ptr[1:])
+    ci = np.concatenate(cols).astype(np.int32)
+    W = inputs.CSR(row_ptr, ci, rng.standard_normal(len(ci)).astype(np.float32) * np.float32(0.05), M, K)
+    check(W, 196, f"mix cap {cap}", "gelu")
+    check(W, 196, f"mix cap {cap} permuted", "none", out_permuted=True)
+
+
+@pytest.mark.parametrize("cap", [1, 8])
+def test_scattered_columns_and_many_descriptors(force, cap):
+    """K = 9000 (141 chunks: more than 64 descriptors a program, loaded 64 at a time) with rows
+    whose entries lie at opposite ends of K, so that programs fill in and wait for one another."""
+    force(cap, 2)
+    rng = np.random.default_rng(7300)
+    M, K = 40, 9000
+    mask = rng.random((M, K)) < 0.02
+    mask[::3, : K - 700] = False
+    mask[1::3, 600:] = False
+    mask[5] = rng.random(K) < 0.5
+    rows, ci = np.nonzero(mask)
+    row_ptr = np.zeros(M + 1, dtype=np.int32)
+    np.cumsum(mask.sum(1), out=row_ptr[1:])
+    W = inputs.CSR(row_ptr, ci.astype(np.int32), rng.standard_normal(len(ci)).astype(np.float32), M, K)
+    check(W, 72, f"scattered cap {cap}", bias=False)
+
+
+@pytest.mark.parametrize("cap,N,K", [(1, 4160, 200), (4, 8256, 600), (8, 16384, 520)])
+def test_persistent_items(force, cap, N, K):
+    """More items than workgroups: a workgroup takes several row-blocks and tiles in turn, the
+    chunk numbers of an item rounded up to the ring."""
+    force(cap, 2)
+    W = inputs.pattern_uniform(300, K, 0.05, inputs.CFG_TEST, 7400 + K, 0.05)
+    check(W, N, f"persistent cap {cap}", "relu")
+
+
+@pytest.mark.parametrize("offset", [1, 2])
+def test_misaligned_input(offset):
+    """B not 16-byte aligned runs the 4-byte staging."""
+    W = inputs.pattern_uniform(100, 200, 0.1, inputs.CFG_TEST, 7500, 0.05)
+    check(W, 256, f"offset {offset}", offset=offset)
+
+
+def test_rows_are_independent_of_other_rows_inputs():
+    """A row's result does not read B rows it has no entry for: infinities there leave it
+    finite, as in the panel kernel."""
+    W = inputs.pattern_uniform(64, 128, 0.1, inputs.CFG_TEST, 7600, 0.05)
+    B = torch.ones(128, 64, device=DEV)
+    B[5] = float("inf")
+    hit = np.zeros(64, bool)
+    for i in range(64):
+        hit[i] = 5 in W.col_idx[W.row_ptr[i]:W.row_ptr[i + 1]]
+    with sd.Plan.from_csr(W) as plan:
+        got = run(plan, B, None, "none")
+    assert np.isfinite(got[~hit]).all() and not np.isfinite(got[hit]).any() and hit.any()

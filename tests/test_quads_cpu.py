@@ -1,0 +1,35 @@
+"""Host self-check of the row-quad packings (sdnn_plan_check_host re-walks every program of a
+default plan: each entry once, in its row, in ascending column order, with its weight bits and
+inside the chunks its descriptor states)."""
+import numpy as np
+import pytest
+
+import paper_2101_07948_amd as sd
+from conftest import random_csr
+
+
+def check(row_ptr, col_idx, values, M, K, **kw):
+    info = sd.plan_check_host(row_ptr, col_idx, values, M, K, **kw)
+    assert info["nnz"] == len(col_idx) and info["packings"] == 5
+
+
+@pytest.mark.parametrize("M,K,density", [(1, 1, 1.0), (7, 64, 0.5), (33, 65, 0.3), (100, 513, 0.02),
+                                         (257, 700, 0.9), (40, 9000, 0.01)])
+def test_random_patterns(M, K, density):
+    rp, ci, v, _ = random_csr(np.random.default_rng([M, K]), M, K, density)
+    check(rp, ci, v, M, K)
+    check(rp, ci, v, M, K, out_permuted=True)
+    check(rp, ci, v, M, K, split_chunks=2)
+
+
+def test_empty_and_extreme_rows():
+    """No entries at all, one full row among empty ones, and rows at opposite ends of K (fillers
+    everywhere, more than 64 descriptors in a program)."""
+    check(np.zeros(6, np.int32), np.zeros(0, np.int32), np.zeros(0, np.float32), 5, 100)
+    K = 20000
+    rp = np.array([0, 0, K, K, K, K, K, K, K], np.int32)
+    check(rp, np.arange(K, dtype=np.int32), np.ones(K, np.float32), 8, K)
+    lo, hi = np.arange(0, 300), np.arange(K - 300, K)
+    cols = np.concatenate([lo, hi, lo, hi, np.arange(0, K, 70)]).astype(np.int32)
+    rp = np.cumsum([0, 300, 300, 300, 300, len(range(0, K, 70))]).astype(np.int32)
+    check(rp, cols, np.ones(len(cols), np.float32), 5, K)
