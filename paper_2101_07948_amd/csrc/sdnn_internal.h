@@ -285,11 +285,13 @@ void launch_shape(const sdnn_plan_s* p, int32_t N, int32_t* panel_rows, int32_t*
 hipError_t tune_spmm(sdnn_plan_s* p, const float* B, float* C, int32_t N, hipStream_t stream,
                      TunedShape* chosen);
 // The row-quad kernel (sdnn_quad.hip): whether it serves the plan's calls at N columns, the
-// launch it picks at N, and its launch.
+// launch it picks at N, and its launch (conv_hwn: H, W and the images of a 3x3 convolution
+// whose input is B, or null).
 bool quads_serve(const sdnn_plan_s* p, int32_t N);
 QuadCfg quad_shape(const sdnn_plan_s* p, int32_t N);
 hipError_t launch_quads(const sdnn_plan_s* p, const float* B, float* C, int32_t N,
-                        const float* bias, int epi, const QuadCfg& cfg, hipStream_t stream);
+                        const float* bias, int epi, const int32_t* conv_hwn, const QuadCfg& cfg,
+                        hipStream_t stream);
 hipError_t launch_dense(const float* W, const float* B, float* C, int32_t M, int32_t K, int32_t N,
                         const float* bias, int epi, hipStream_t stream);
 }  // namespace sdnn

@@ -879,7 +879,7 @@ hipError_t launch_spmm(const sdnn_plan_s* p, const float* B, float* C, int32_t N
     for (int i = 0; i < p->ntuned; ++i)
       if (p->tuned[i].N == N) t = &p->tuned[i];
     if (!t || t->quads)
-      return launch_quads(p, B, C, N, bias, epi, t ? t->quad : quad_shape(p, N), stream);
+      return launch_quads(p, B, C, N, bias, epi, nullptr, t ? t->quad : quad_shape(p, N), stream);
   }
   return launch_panels(p, B, C, N, bias, epi, nullptr, nullptr, nullptr, 0, stream);
 }
@@ -952,10 +952,10 @@ hipError_t tune_spmm(sdnn_plan_s* p, const float* B, float* C, int32_t N, hipStr
     for (int pass = 0; pass < 2; ++pass)
       for (size_t i = 0; i < quads.size() && err == hipSuccess; ++i) {
         for (int r = 0; r < 2 && err == hipSuccess; ++r)
-          err = launch_quads(p, B, C, N, nullptr, 0, quads[i], stream);
+          err = launch_quads(p, B, C, N, nullptr, 0, nullptr, quads[i], stream);
         if (err == hipSuccess) err = hipEventRecord(e0, stream);
         for (int r = 0; r < 8 && err == hipSuccess; ++r)
-          err = launch_quads(p, B, C, N, nullptr, 0, quads[i], stream);
+          err = launch_quads(p, B, C, N, nullptr, 0, nullptr, quads[i], stream);
         if (err == hipSuccess) err = hipEventRecord(e1, stream);
         if (err == hipSuccess) err = hipEventSynchronize(e1);
         float ms = 0.0f;
@@ -1061,6 +1061,8 @@ hipError_t scratch_address(int device, float** out) {
 hipError_t launch_conv3x3(const sdnn_plan_s* p, const float* X, float* C, int32_t H, int32_t W,
                           int32_t NB, const float* bias, int epi, hipStream_t stream) {
   const int32_t hwn[3] = {H, W, NB};
+  if (quads_serve(p, H * W * NB))
+    return launch_quads(p, X, C, H * W * NB, bias, epi, hwn, quad_shape(p, H * W * NB), stream);
   return launch_panels(p, X, C, H * W * NB, bias, epi, hwn, nullptr, nullptr, 0, stream);
 }
 
@@ -1068,6 +1070,8 @@ hipError_t launch_conv3x3_split(const sdnn_plan_s* p, const float* X, float* C, 
                                 int32_t W, int32_t NB, const float* bias, int epi, int splits,
                                 float* ws, hipStream_t stream) {
   const int32_t hwn[3] = {H, W, NB};
+  if (split_runs_of(p, H * W * NB, splits, true, nullptr) == 1)
+    return launch_conv3x3(p, X, C, H, W, NB, bias, epi, stream);
   return launch_panels(p, X, C, H * W * NB, bias, epi, hwn, nullptr, ws, splits, stream);
 }
 

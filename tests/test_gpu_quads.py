@@ -137,3 +137,25 @@ def test_rows_are_independent_of_other_rows_inputs():
     with sd.Plan.from_csr(W) as plan:
         got = run(plan, B, None, "none")
     assert np.isfinite(got[~hit]).all() and not np.isfinite(got[hit]).any() and hit.any()
+
+
+@pytest.mark.parametrize("cap", [1, 4, 8])
+@pytest.mark.parametrize("OC,IC,H,W,NB", [(5, 1, 1, 1, 4), (9, 3, 5, 7, 4), (33, 8, 3, 11, 12),
+                                          (40, 64, 9, 9, 8)])
+def test_convolution(force, cap, OC, IC, H, W, NB):
+    """The virtual operand of a 3x3 convolution: a single pixel, ragged tiles, K = 9 to 576
+    (past the ring), every border, against the oracle and the panel kernel."""
+    force(cap, 3)
+    L = inputs.conv_layer(OC, IC, H, W, NB, 0.6, layer=700 + OC + IC, epi="relu")
+    X = torch.from_numpy(L.X).to(DEV)
+    bt = torch.from_numpy(L.bias).to(DEV)
+    out = []
+    for kw in ({}, {"panel_rows": 4}):
+        with sd.Plan.from_csr(L.F, **kw) as plan:
+            C = torch.full((OC, H, W, NB), float("nan"), device=DEV)
+            plan.conv3x3(X, C, bt, "relu")
+            torch.cuda.synchronize()
+            out.append(C.cpu().numpy())
+    ref, bound = oracle.conv3x3_f64(L.F.row_ptr, L.F.col_idx, L.F.values, L.X, L.bias, "relu")
+    assert (np.abs(out[0].astype(np.float64) - ref) <= tol_fp32(bound, "relu")).all()
+    assert np.array_equal(out[0], out[1])
