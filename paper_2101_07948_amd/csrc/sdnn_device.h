@@ -10,24 +10,32 @@
 namespace sdnn {
 namespace {
 
-// GELU(x) = x Phi(x) = 0.5 x (1 + erf(x / sqrt 2)) (the exact erf form).  erf(z) for
-// z >= 0 comes from Abramowitz & Stegun 7.1.26 (Hastings' approximation, absolute error
-// at most 1.5e-7): erf(z) = 1 - q, q = t (a1 + t (a2 + t (a3 + t (a4 + t a5)))) e^(-z^2),
-// t = 1 / (1 + p z); with erf(-z) = -erf(z), GELU(x) = 0.5 x (2 - q) for x >= 0 and
-// 0.5 x q for x < 0 (no cancellation on the negative side).  The reciprocal and the
-// exponential are the hardware's (v_rcp_f32, v_exp_f32, about 1 ulp); the result is within
-// 0.5 |x| * 4e-7 of the exact GELU, far inside the 1e-6 floor of the parity bar at the
-// |x| these layers reach, and costs about a third of the library erff's instructions.
+// GELU(x) = x Phi(x) = 0.5 x (1 + erf(x / sqrt 2)) (the exact erf form).  With z = |x| / sqrt 2
+// and erfc(z) = t (a1 + t (a2 + t (a3 + t (a4 + t a5)))) e^(-z^2), t = 1 / (1 + p z) (Abramowitz &
+// Stegun 7.1.26, Hastings' approximation, absolute error at most 1.5e-7),
+//     GELU(x) = max(x, 0) - 0.5 |x| erfc(z)
+// for either sign (no cancellation: the second term is at most half the first, or alone).
+// Evaluated on y = |x| sqrt(0.5 log2 e), so that e^(-z^2) = 2^(-y^2), with the factor 0.5 |x| / y
+// folded into the coefficients; their last bits (and p's) were then searched for the smallest
+// error in float arithmetic, because the rounded ones no longer sum to erfc(0) = 1.  The
+// reciprocal and the exponential are the hardware's (v_rcp_f32, v_exp_f32, about 1 ulp).  The
+// result is within 0.5 |x| * 6e-7 of the exact GELU, far inside the 1e-6 floor of the parity bar
+// at the |x| these layers reach; against the coefficients as printed, over |x| distributed
+// N(0, 0.005^2) to N(0, 5^2), the 2-norm error is 0.92-1.006 of theirs.  12 plain instructions
+// and the two special ones, where the two-sided form took 18: on the 3072 x 768 layer at
+// N = 16384 the GELU of 50 M outputs is a third of the vector instructions (107.7 -> 103.1 us).
 __device__ __forceinline__ float gelu(float x) {
-  const float z = fabsf(x) * 0.70710678118654752f;
-  const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f, z, 1.0f));
-  float poly = fmaf(t, 1.061405429f, -1.453152027f);
-  poly = fmaf(t, poly, 1.421413741f);
-  poly = fmaf(t, poly, -0.284496736f);
-  poly = fmaf(t, poly, 0.254829592f);
-  poly *= t;
-  const float q = poly * __builtin_amdgcn_exp2f(-z * z * 1.4426950408889634f);
-  return 0.5f * x * (x >= 0.0f ? 2.0f - q : q);
+  const float y = fabsf(x) * 0.8493217825889587f;
+  const float e = __builtin_amdgcn_exp2f(-(y * y));
+  const float t = __builtin_amdgcn_rcpf(fmaf(y, 0.27273744344711304f, 1.0f));
+  float q = fmaf(t, 0.6248548030853271f, -0.855477511882782f);
+  q = fmaf(t, q, 0.8367929458618164f);
+  q = fmaf(t, q, -0.16748465597629547f);
+  q = fmaf(t, q, 0.15001946687698364f);
+  q *= t;
+  q *= e;
+  // (an infinite x has q = 0: its factor stays finite)
+  return fmaf(-fminf(y, 3.402823466e38f), q, fmaxf(x, 0.0f));
 }
 
 // C is written once and not read again by the kernel: its stores are non-temporal, so the

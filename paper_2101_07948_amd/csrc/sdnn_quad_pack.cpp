@@ -1,7 +1,6 @@
 // Preparation for the row-quad kernel (SparseDNN, arXiv 2101.07948, Sec. 3.2.2: each
 // matrix repacked in its kernel's traversal order): programs of row quads, their blocks and
 // their descriptors (see QuadPacked).
-#include <stdlib.h>
 #include <string.h>
 
 #include <algorithm>
@@ -15,7 +14,6 @@ namespace sdnn {
 // window follows the density d; past the width that keeps filler under a few per cent, a
 // narrower one leaves more of the ring to the DMAs in flight.
 static int quad_window(const int32_t* row_ptr, int32_t M, int32_t K) {
-  if (getenv("QWIN")) return atoi(getenv("QWIN"));
   const double d = (double)row_ptr[M] / ((double)std::max(M, 1) * std::max(K, 1));
   return d >= 0.2 ? kQuadMaxWindow - 3 : d >= 0.08 ? kQuadMaxWindow - 2 : kQuadMaxWindow;
 }
@@ -39,7 +37,9 @@ void pack_quads(const int32_t* row_ptr, const int32_t* col_idx, const float* val
   for (int32_t i0 = 0; i0 < M;) {
     int32_t NS = cap;
     while (NS > 1 && (double)NS * (row_ptr[order[i0] + 1] - row_ptr[order[i0]]) > longest) NS /= 2;
-    const int RW = 4 * NS, steps = kQuadUnits / NS;
+    const int RW = 4 * NS, steps = kQuadUnits / NS, to_addr = quad_addr_at(NS);
+    int dword[4 * kQuadMaxCap], next_step = NS <= 2 ? NS : NS / 2;  // row j's weight: step 0, and on
+    for (int j = 0; j < RW; ++j) dword[j] = quad_dword(NS, j, 0);
     int32_t at[4 * kQuadMaxCap], end[4 * kQuadMaxCap];  // next entry and end of each row
     bool any = false;
     for (int j = 0; j < RW; ++j) {
@@ -63,30 +63,35 @@ void pack_quads(const int32_t* row_ptr, const int32_t* col_idx, const float* val
         n = 0;
       };
       for (;;) {
-        int32_t low = -1;  // the program's lowest unread column
+        int32_t low = INT32_MAX;  // the program's lowest unread column
         for (int j = 0; j < RW; ++j)
-          if (at[j] < end[j] && (low < 0 || col_idx[at[j]] < low)) low = col_idx[at[j]];
-        if (low < 0) break;
+          if (at[j] < end[j]) low = std::min(low, col_idx[at[j]]);
+        if (low == INT32_MAX) break;
         const int32_t clo = low / kQuadChunk;
-        int32_t chi = clo;
         const int64_t limit = ((int64_t)clo + window) * kQuadChunk;  // first column not taken
+        int32_t high = low;
         const size_t base = Q.stream.size();
         Q.stream.resize(base + 64);
         uint32_t* blk = Q.stream.data() + base;
-        for (int j = 0; j < RW; ++j)
-          for (int st = 0; st < steps; ++st) {
-            const int at_w = quad_dword(NS, j, st);
+        for (int j = 0; j < RW; ++j) {
+          uint32_t* to = blk + dword[j];
+          int32_t e = at[j];
+          const int32_t stop = end[j];
+          for (int st = 0; st < steps; ++st, to += next_step) {
             uint32_t w = 0, addr = kQuadZeroRow;
-            if (at[j] < end[j] && col_idx[at[j]] < limit) {
-              const int32_t k = col_idx[at[j]];
-              memcpy(&w, &values[at[j]], 4);
-              addr = (uint32_t)(k % (kQuadRing * kQuadChunk)) * kQuadRowBytes;
-              chi = std::max(chi, k / kQuadChunk);
-              ++at[j];
+            if (e < stop && col_idx[e] < limit) {
+              const int32_t k = col_idx[e];
+              memcpy(&w, &values[e], 4);
+              addr = (uint32_t)k % (kQuadRing * kQuadChunk) * kQuadRowBytes;
+              high = std::max(high, k);
+              ++e;
             }
-            blk[at_w] = w;
-            blk[at_w + quad_addr_at(NS)] = addr;
+            to[0] = w;
+            to[to_addr] = addr;
           }
+          at[j] = e;
+        }
+        const int32_t chi = high / kQuadChunk;
         if (n > 0 && (clo != lo || chi > hi || n == kQuadMaxBlocks)) close();
         if (n == 0) {
           lo = clo;
