@@ -289,15 +289,43 @@ __device__ __forceinline__ void produce(const float* B, const QuadArgs& a, int p
 
 // ---- kernel -----------------------------------------------------------------------------
 
-// One program of a consumer wave: its loop, then the epilogue of its 4 NS rows.  Lane group g
-// of set q holds row q * kRows + g, the lane kVecs times four columns.
+// The epilogue of a program's 4 NS rows, one copy per activation: with the activation chosen per
+// element, each element was a basic block of its own, whose reciprocal and exponential nothing
+// overlapped.  Lane group g of set q holds row q * kRows + g, the lane kVecs times four
+// columns (of groups of 4 lanes, the i-th vector is quarter i ^ (g % 4)).
+template <int NS, int STAGE, int EPI, int SETS, int ACCS>
+__device__ __forceinline__ void store_program(const group_acc_t<ACCS> (&acc)[SETS], const int (&out)[SETS],
+                                              const float (&bb)[SETS], float* C, int n0, int lane, int N) {
+  constexpr int kGroup = NS <= 2 ? 16 : 4, kVecs = ACCS / 4;
+  const int quarter = lane / kGroup % 4;
+#pragma unroll
+  for (int q = 0; q < SETS; ++q) {
+    float v[ACCS];
+#pragma unroll
+    for (int k = 0; k < ACCS; ++k) v[k] = activation(acc[q][k] + bb[q], EPI);
+    if (out[q] < 0) continue;
+    float* c = C + (size_t)out[q] * N;
+#pragma unroll
+    for (int i = 0; i < kVecs; ++i) {
+      const int n = n0 + 4 * (lane % kGroup) + 4 * kGroup * (kVecs > 1 ? i ^ quarter : 0);
+      if (STAGE != kQuadDword) {
+        if (n < N) store_c4(c + n, v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]);
+      } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          if (n + k < N) store_c1(c + n + k, v[4 * i + k]);
+      }
+    }
+  }
+}
+
+// One program of a consumer wave: its loop, then the epilogue of its rows.
 template <int NS, int STAGE>
 __device__ __forceinline__ void run_program(QuadConsumer& ca, bool entries, const int32_t* rows,
                                             const int32_t* outs, float* C, const float* bias, int n0,
                                             int lane, const QuadArgs& a) {
   constexpr int kGroup = NS <= 2 ? 16 : 4, kRows = 64 / kGroup, kSets = 4 * NS / kRows;
-  constexpr int kVecs = kQuadTileCols / (4 * kGroup);
-  const int quarter = lane / kGroup % 4;  // group g's i-th vector is quarter i ^ (g % 4)
+  constexpr int kAccs = kQuadTileCols / kGroup;
   int out[kSets];
   float bb[kSets];
 #pragma unroll
@@ -307,37 +335,21 @@ __device__ __forceinline__ void run_program(QuadConsumer& ca, bool entries, cons
     const int src = rows[j];
     bb[q] = bias && src >= 0 ? bias[src] : 0.0f;
   }
-  group_acc_t<4 * kVecs> acc[kSets];
+  group_acc_t<kAccs> acc[kSets];
 #pragma unroll
   for (int q = 0; q < kSets; ++q)
 #pragma unroll
-    for (int k = 0; k < 4 * kVecs; ++k) acc[q][k] = 0.0f;
+    for (int k = 0; k < kAccs; ++k) acc[q][k] = 0.0f;
   if (entries) {
-    ca.vlane = (uint32_t)(lane % kGroup) * 16u + (kVecs > 1 ? (uint32_t)quarter * 64u : 0u);
+    ca.vlane = (uint32_t)(lane % kGroup) * 16u + (kAccs > 4 ? (uint32_t)(lane / kGroup % 4) * 64u : 0u);
     if constexpr (NS == 1) consume_quads1(acc, ca);
     if constexpr (NS == 2) consume_quads2(acc, ca);
     if constexpr (NS == 4) consume_quads4(acc, ca);
     if constexpr (NS == 8) consume_quads8(acc, ca);
   }
-#pragma unroll
-  for (int q = 0; q < kSets; ++q) {
-    if (out[q] < 0) continue;
-    float* c = C + (size_t)out[q] * a.N;
-#pragma unroll
-    for (int i = 0; i < kVecs; ++i) {
-      const int n = n0 + 4 * (lane % kGroup) + 4 * kGroup * (kVecs > 1 ? i ^ quarter : 0);
-      float v[4];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) v[k] = activation(acc[q][4 * i + k] + bb[q], a.epi);
-      if (STAGE != kQuadDword) {
-        if (n < a.N) store_c4(c + n, v[0], v[1], v[2], v[3]);
-      } else {
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-          if (n + k < a.N) store_c1(c + n + k, v[k]);
-      }
-    }
-  }
+  if (a.epi == SDNN_EPI_GELU) store_program<NS, STAGE, SDNN_EPI_GELU>(acc, out, bb, C, n0, lane, a.N);
+  else if (a.epi == SDNN_EPI_RELU) store_program<NS, STAGE, SDNN_EPI_RELU>(acc, out, bb, C, n0, lane, a.N);
+  else store_program<NS, STAGE, SDNN_EPI_NONE>(acc, out, bb, C, n0, lane, a.N);
 }
 
 // STAGE: 16-byte staging and stores (N % 4 == 0, B and C 16-byte aligned) or 4-byte ones;
