@@ -319,11 +319,28 @@ __device__ __forceinline__ void store_program(const group_acc_t<ACCS> (&acc)[SET
   }
 }
 
-// One program of a consumer wave: its loop, then the epilogue of its rows.
+// A wave's place in its workgroup's items.
+struct QuadCursor {
+  int it, nitems, item, tile, prog, stratum;
+  __device__ __forceinline__ void find(const QuadArgs& a) {  // the program of `item`
+    tile = item / a.n_rb;
+    const int rb = item - tile * a.n_rb;
+    prog = stratum * a.n_rb + ((stratum & 1) ? a.n_rb - 1 - rb : rb);
+  }
+  __device__ __forceinline__ bool next(const QuadArgs& a) {
+    item += a.total_wg;
+    return ++it < nitems;
+  }
+};
+
+// One program of a consumer wave over the items that run it in a row (when the row-blocks
+// divide the workgroups, all of the wave's): its loop and the epilogue of its rows per item.
+// The rows' tables are read once; read per item, their two dependent loads stood between the
+// items of every wave.
 template <int NS, int STAGE>
 __device__ __forceinline__ void run_program(QuadConsumer& ca, bool entries, const int32_t* rows,
-                                            const int32_t* outs, float* C, const float* bias, int n0,
-                                            int lane, const QuadArgs& a) {
+                                            const int32_t* outs, float* C, const float* bias,
+                                            QuadCursor& cur, int lane, const QuadArgs& a) {
   constexpr int kGroup = NS <= 2 ? 16 : 4, kRows = 64 / kGroup, kSets = 4 * NS / kRows;
   constexpr int kAccs = kQuadTileCols / kGroup;
   int out[kSets];
@@ -335,21 +352,31 @@ __device__ __forceinline__ void run_program(QuadConsumer& ca, bool entries, cons
     const int src = rows[j];
     bb[q] = bias && src >= 0 ? bias[src] : 0.0f;
   }
-  group_acc_t<kAccs> acc[kSets];
+  ca.vlane = (uint32_t)(lane % kGroup) * 16u + (kAccs > 4 ? (uint32_t)(lane / kGroup % 4) * 64u : 0u);
+  const int prog = cur.prog;
+  do {
+    ca.chunk_base = (uint32_t)(cur.it * a.ring_chunks);
+    ca.next_progress = cur.it + 1 < cur.nitems ? (uint32_t)((cur.it + 1) * a.ring_chunks) : kProgressEnd;
+    group_acc_t<kAccs> acc[kSets];
 #pragma unroll
-  for (int q = 0; q < kSets; ++q)
+    for (int q = 0; q < kSets; ++q)
 #pragma unroll
-    for (int k = 0; k < kAccs; ++k) acc[q][k] = 0.0f;
-  if (entries) {
-    ca.vlane = (uint32_t)(lane % kGroup) * 16u + (kAccs > 4 ? (uint32_t)(lane / kGroup % 4) * 64u : 0u);
-    if constexpr (NS == 1) consume_quads1(acc, ca);
-    if constexpr (NS == 2) consume_quads2(acc, ca);
-    if constexpr (NS == 4) consume_quads4(acc, ca);
-    if constexpr (NS == 8) consume_quads8(acc, ca);
-  }
-  if (a.epi == SDNN_EPI_GELU) store_program<NS, STAGE, SDNN_EPI_GELU>(acc, out, bb, C, n0, lane, a.N);
-  else if (a.epi == SDNN_EPI_RELU) store_program<NS, STAGE, SDNN_EPI_RELU>(acc, out, bb, C, n0, lane, a.N);
-  else store_program<NS, STAGE, SDNN_EPI_NONE>(acc, out, bb, C, n0, lane, a.N);
+      for (int k = 0; k < kAccs; ++k) acc[q][k] = 0.0f;
+    if (entries) {
+      if constexpr (NS == 1) consume_quads1(acc, ca);
+      if constexpr (NS == 2) consume_quads2(acc, ca);
+      if constexpr (NS == 4) consume_quads4(acc, ca);
+      if constexpr (NS == 8) consume_quads8(acc, ca);
+    } else if (lane == 0) {
+      lds_write(ca.prog_addr, ca.next_progress);  // no entries: only epi(bias)
+    }
+    const int n0 = cur.tile * kQuadTileCols;
+    if (a.epi == SDNN_EPI_GELU) store_program<NS, STAGE, SDNN_EPI_GELU>(acc, out, bb, C, n0, lane, a.N);
+    else if (a.epi == SDNN_EPI_RELU) store_program<NS, STAGE, SDNN_EPI_RELU>(acc, out, bb, C, n0, lane, a.N);
+    else store_program<NS, STAGE, SDNN_EPI_NONE>(acc, out, bb, C, n0, lane, a.N);
+    if (!cur.next(a)) return;
+    cur.find(a);
+  } while (cur.prog == prog);
 }
 
 // STAGE: 16-byte staging and stores (N % 4 == 0, B and C 16-byte aligned) or 4-byte ones;
@@ -401,18 +428,21 @@ __global__ __launch_bounds__(1024) void spmm_quad_kernel(
   }
 
   const int g4 = wave >> 2, i4 = wave & 3;
-  const int stratum = (g4 & 1) && 4 * g4 + 4 <= nc ? 4 * g4 + 3 - i4 : wave;
-  for (int it = 0; it < nitems; ++it) {
-    const int item = lin + it * a.total_wg;
-    const int tile = item / a.n_rb, rb = item - tile * a.n_rb;
-    const uint32_t cbase = (uint32_t)(it * a.ring_chunks);
-    const uint32_t next = it + 1 < nitems ? (uint32_t)((it + 1) * a.ring_chunks) : kProgressEnd;
-    const int prog = stratum * a.n_rb + ((stratum & 1) ? a.n_rb - 1 - rb : rb);
-    if (prog >= a.nprogs) {
-      if (lane == 0) lds_write(progress, next);
+  QuadCursor cur;
+  cur.it = 0;
+  cur.nitems = nitems;
+  cur.item = lin;
+  cur.stratum = (g4 & 1) && 4 * g4 + 4 <= nc ? 4 * g4 + 3 - i4 : wave;
+  cur.find(a);
+  while (cur.it < nitems) {
+    if (cur.prog >= a.nprogs) {  // no program in this row-block
+      if (lane == 0)
+        lds_write(progress, cur.it + 1 < nitems ? (uint32_t)((cur.it + 1) * a.ring_chunks) : kProgressEnd);
+      cur.next(a);
+      cur.find(a);
       continue;
     }
-    const QuadProgram P = progs[prog];
+    const QuadProgram P = progs[cur.prog];
     QuadConsumer ca;
     ca.stream = stream + (size_t)P.start * 64;
     ca.descs = descs + P.desc;
@@ -421,15 +451,12 @@ __global__ __launch_bounds__(1024) void spmm_quad_kernel(
     ca.ready_addr = kCtl;
     ca.overrun_addr = kCtl + 128u;
     ca.poll_budget = a.poll_budget;
-    ca.chunk_base = cbase;
-    ca.next_progress = next;
-    const int at = prog * (4 * CAP);
-    const int n0 = tile * kQuadTileCols;
-    if (P.start < 0 && lane == 0) lds_write(progress, next);  // no entries: only epi(bias)
-    if (CAP == 8 && P.NS == 8) run_program<8, STAGE>(ca, P.start >= 0, rows + at, outs + at, C, bias, n0, lane, a);
-    else if (CAP >= 4 && P.NS == 4) run_program<4, STAGE>(ca, P.start >= 0, rows + at, outs + at, C, bias, n0, lane, a);
-    else if (CAP >= 2 && P.NS == 2) run_program<2, STAGE>(ca, P.start >= 0, rows + at, outs + at, C, bias, n0, lane, a);
-    else run_program<1, STAGE>(ca, P.start >= 0, rows + at, outs + at, C, bias, n0, lane, a);
+    const int32_t* r = rows + (size_t)cur.prog * (4 * CAP);
+    const int32_t* o = outs + (size_t)cur.prog * (4 * CAP);
+    if (CAP == 8 && P.NS == 8) run_program<8, STAGE>(ca, P.start >= 0, r, o, C, bias, cur, lane, a);
+    else if (CAP >= 4 && P.NS == 4) run_program<4, STAGE>(ca, P.start >= 0, r, o, C, bias, cur, lane, a);
+    else if (CAP >= 2 && P.NS == 2) run_program<2, STAGE>(ca, P.start >= 0, r, o, C, bias, cur, lane, a);
+    else run_program<1, STAGE>(ca, P.start >= 0, r, o, C, bias, cur, lane, a);
   }
 }
 
