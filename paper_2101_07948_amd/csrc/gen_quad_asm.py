@@ -34,7 +34,7 @@ Register plan (pinned in the asm statement): v[20:23] the stream blocks in fligh
 loaded again as soon as it is consumed), v[24:27] the producers' ready words while polling;
 else, for groups of 4, v24 and v30 the weights and v[25:27] 64, 128, 192; v28 4 * lane, v29 64
 descriptors (one per lane, read with v_readlane), v30 temp, v31 the lane's byte offset in a
-B row, v[32:63] / v[64:95] B values of
+B row (with the item's slot flip: the address is the stream's XOR v31), v[32:63] / v[64:95] B values of
 the block being multiplied / fetched, v[96:...] accumulators (4 or 16 per set).
 
 Per block g: at the end of a descriptor, the sync point of the next one; addresses and
@@ -76,12 +76,12 @@ def address_phase(e, vb, ns):
     if ns <= 2:
         for u in range(UNITS):
             v = vb + 4 * u
-            L += [f"v_or_b32_dpp v{v}, v{e}, v31 {dpp(UNITS + u, ns)}",
+            L += [f"v_xor_b32_dpp v{v}, v{e}, v31 {dpp(UNITS + u, ns)}",
                   f"ds_read_b128 v[{v}:{v + 3}], v{v}"]
     else:
         for u in range(2):
             v = vb + 16 * u
-            L.append(f"v_or_b32_dpp v{v}, v{e}, v31 {dpp(2 * u + 1, ns)}")
+            L.append(f"v_xor_b32_dpp v{v}, v{e}, v31 {dpp(2 * u + 1, ns)}")
             for i in (1, 2, 3):             # quarters i ^ (g % 4): offsets 64, 128, 192 flipped
                 L.append(f"v_xor_b32 v{v + 4 * i}, v{QREG + i - 1}, v{v}")
             for i in range(4):

@@ -65,17 +65,16 @@ static_assert(kQuadAsmLoShift == kQuadLoShift && kQuadAsmHiShift == kQuadHiShift
 
 constexpr uint32_t kProgressEnd = 0x7fffffffu;
 constexpr int kPollBudgetQuad = 1 << 22;
-// LDS: the ring, a row of zeros (read by the filler entries), then the control words:
-// ready[4] at +0, progress[16] at +64, the overrun word at +128.
-constexpr int kRingB = kQuadRing * kQuadChunk * kQuadRowBytes;
-constexpr int kCtl = kRingB + kQuadRowBytes;
-constexpr int kLdsBytes = kCtl + 256;
-static_assert(kQuadZeroRow == kRingB, "the filler entries' row of zeros follows the ring");
+// LDS: the ring, a row of zeros (read by the filler entries), the control words (ready[4] at
+// +0, progress[16] at +64, the overrun word at +128), and the second row of zeros.
+constexpr int kCtl = kQuadZeroRow + kQuadRowBytes;
+constexpr int kLdsBytes = (kQuadZeroRow | kQuadFlip) + kQuadRowBytes;
+static_assert(kCtl + 256 <= (kQuadZeroRow | kQuadFlip) && kLdsBytes <= 160 * 1024, "LDS layout");
 constexpr int kMaxQuadConsumers = 16 - kQuadProducers;
 
 struct QuadArgs {
   int32_t K, N, nchunks, nprogs;
-  int32_t ring_chunks;  // nchunks rounded up to the ring: chunk numbers an item takes up
+  int32_t ring_chunks;  // chunk numbers an item takes up: nchunks, rounded up to half the ring
   int32_t n_rb, n_tiles, total_wg, per_xcd, epi;
   uint32_t poll_budget;
   int32_t H, W, NB;  // image geometry of a 3x3 convolution (B is then the input X)
@@ -215,7 +214,7 @@ __device__ __forceinline__ void stage_chunk(const QuadArgs& a, const float* B, i
 // so every chunk below the smallest ready word has landed.  Two chunks are in flight: a
 // chunk's DMAs go out before the previous one's are waited for.  An item takes ring_chunks
 // chunk numbers; those past nchunks hold no rows (an item's chunk c keeps ring slot
-// c % kQuadRing).
+// c % kQuadRing, or c + 4).
 template <int STAGE>
 __device__ __forceinline__ void produce(const float* B, const QuadArgs& a, int prod, int lane, int item,
                         int nitems) {
@@ -256,7 +255,7 @@ __device__ __forceinline__ void produce(const float* B, const QuadArgs& a, int p
       }
     }
     const bool real = ci < a.nchunks;
-    const uint32_t slot = (g % kQuadRing) * (kQuadChunk * kQuadRowBytes);
+    const uint32_t slot = quad_slot(g % kQuadRing);
     if constexpr (STAGE == kQuadConv) {
       if (real) stage_conv(a, conv, n0, ci * kQuadChunk, slot, lane);
     } else {
@@ -352,10 +351,11 @@ __device__ __forceinline__ void run_program(QuadConsumer& ca, bool entries, cons
     const int src = rows[j];
     bb[q] = bias && src >= 0 ? bias[src] : 0.0f;
   }
-  ca.vlane = (uint32_t)(lane % kGroup) * 16u + (kAccs > 4 ? (uint32_t)(lane / kGroup % 4) * 64u : 0u);
+  const uint32_t vlane = (uint32_t)(lane % kGroup) * 16u + (kAccs > 4 ? (uint32_t)(lane / kGroup % 4) * 64u : 0u);
   const int prog = cur.prog;
   do {
     ca.chunk_base = (uint32_t)(cur.it * a.ring_chunks);
+    ca.vlane = vlane ^ (ca.chunk_base & 4u ? kQuadFlip : 0u);
     ca.next_progress = cur.it + 1 < cur.nitems ? (uint32_t)((cur.it + 1) * a.ring_chunks) : kProgressEnd;
     group_acc_t<kAccs> acc[kSets];
 #pragma unroll
@@ -415,7 +415,8 @@ __global__ __launch_bounds__(1024) void spmm_quad_kernel(
     if (lane == 0) lds_write(kCtl + 4u * prod, (uint32_t)prod);                    // nothing landed
     if (prod == 0 && lane >= nc && lane < 16) lds_write(kCtl + 64u + 4u * lane, kProgressEnd);  // absent
     if (prod == 0 && lane == 0) lds_write(kCtl + 128u, 0u);                        // no overrun
-    if (prod == 1) lds_write(kRingB + 4u * lane, 0u);                              // the row of zeros
+    if (prod == 1) lds_write(kQuadZeroRow + 4u * lane, 0u);                        // the rows of zeros
+    if (prod == 2) lds_write((kQuadZeroRow | kQuadFlip) + 4u * lane, 0u);
   } else if (lane == 0) {
     lds_write(progress, 0u);
   }
@@ -509,7 +510,7 @@ QuadCfg choose_quads(const sdnn_plan_s* p, int N) {
     const double lat = (hex ? 0.127 : 0.085) * 0.5 * (mean + d.longest) + (hex ? 0.080 : 0.107) * chunks;
     for (int w = std::min(2, d.nprogs); w <= std::min(kMaxQuadConsumers, d.nprogs); ++w) {
       const int64_t items = tiles * ((d.nprogs + w - 1) / w), rounds = (items + cus - 1) / cus;
-      const int staged = rounds > 1 ? (chunks + kQuadRing - 1) / kQuadRing * kQuadRing : chunks;
+      const int staged = rounds > 1 ? (chunks + 3) / 4 * 4 : chunks;
       const double t = rounds * (lat + (hex ? 0.011 : 0.036) * mean * std::max(0.25 * w, 1.0) +
                                  0.104 * staged + (d.cap == 8 ? 0.0083 : 0.0057) * 4.0 * d.cap * w);
       if (best_t < 0.0 || t < best_t) {
@@ -549,7 +550,7 @@ hipError_t launch_quads(const sdnn_plan_s* p, const float* B, float* C, int32_t 
   args.K = p->K;
   args.N = N;
   args.nchunks = (p->K + kQuadChunk - 1) / kQuadChunk;
-  args.ring_chunks = (args.nchunks + kQuadRing - 1) / kQuadRing * kQuadRing;
+  args.ring_chunks = (args.nchunks + 3) / 4 * 4;
   args.nprogs = d.nprogs;
   args.n_rb = (d.nprogs + waves - 1) / waves;
   args.n_tiles = (N + kQuadTileCols - 1) / kQuadTileCols;

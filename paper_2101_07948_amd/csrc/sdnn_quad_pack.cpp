@@ -82,7 +82,7 @@ void pack_quads(const int32_t* row_ptr, const int32_t* col_idx, const float* val
             if (e < stop && col_idx[e] < limit) {
               const int32_t k = col_idx[e];
               memcpy(&w, &values[e], 4);
-              addr = (uint32_t)k % (kQuadRing * kQuadChunk) * kQuadRowBytes;
+              addr = quad_address(k);
               high = std::max(high, k);
               ++e;
             }
@@ -194,7 +194,7 @@ bool check_quads(const int32_t* row_ptr, const int32_t* col_idx, const float* va
             uint32_t bits;
             memcpy(&bits, &values[at[j]], 4);
             const uint32_t c = (uint32_t)(k / kQuadChunk);
-            if (bits != w || addr != (uint32_t)(k % (kQuadRing * kQuadChunk)) * kQuadRowBytes ||
+            if (bits != w || addr != quad_address(k) ||
                 c < lo || c > hi)
               return false;
             ++at[j];
