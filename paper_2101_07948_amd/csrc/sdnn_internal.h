@@ -208,6 +208,10 @@ std::vector<uint32_t> narrow_stream(const std::vector<uint32_t>& entries);
 // True if `narrow` is narrow_stream(entries) field by field (decoded independently).
 bool check_narrow_stream(const std::vector<uint32_t>& entries, const std::vector<uint32_t>& narrow);
 
+// Staging kinds of the row-quad kernel: 16-byte pieces and stores (N % 4 == 0, B and C 16-byte
+// aligned), 4-byte ones (any N), and the virtual B of a 3x3 convolution (16-byte pieces of an
+// IC x H x W x NB input).
+enum QuadStage { kQuadVec = 0, kQuadDword = 1, kQuadConv = 2 };
 // Launch of the row-quad kernel: packing (index into sdnn_plan_s::quads), consumer waves.
 struct QuadCfg {
   int32_t pack = 0, waves = 0;
@@ -300,7 +304,7 @@ hipError_t tune_spmm(sdnn_plan_s* p, const float* B, float* C, int32_t N, hipStr
 // launch it picks at N, and its launch (conv_hwn: H, W and the images of a 3x3 convolution
 // whose input is B, or null).
 bool quads_serve(const sdnn_plan_s* p, int32_t N);
-QuadCfg quad_shape(const sdnn_plan_s* p, int32_t N);
+QuadCfg quad_shape(const sdnn_plan_s* p, const float* B, const float* C, int32_t N, bool conv);
 hipError_t launch_quads(const sdnn_plan_s* p, const float* B, float* C, int32_t N,
                         const float* bias, int epi, const int32_t* conv_hwn, const QuadCfg& cfg,
                         hipStream_t stream);

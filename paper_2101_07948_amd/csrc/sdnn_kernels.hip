@@ -879,7 +879,8 @@ hipError_t launch_spmm(const sdnn_plan_s* p, const float* B, float* C, int32_t N
     for (int i = 0; i < p->ntuned; ++i)
       if (p->tuned[i].N == N) t = &p->tuned[i];
     if (!t || t->quads)
-      return launch_quads(p, B, C, N, bias, epi, nullptr, t ? t->quad : quad_shape(p, N), stream);
+      return launch_quads(p, B, C, N, bias, epi, nullptr, t ? t->quad : quad_shape(p, B, C, N, false),
+                          stream);
   }
   return launch_panels(p, B, C, N, bias, epi, nullptr, nullptr, nullptr, 0, stream);
 }
@@ -944,7 +945,7 @@ hipError_t tune_spmm(sdnn_plan_s* p, const float* B, float* C, int32_t N, hipStr
   // the row-quad kernel, where it serves the call: every packing with its most consumer waves
   // and three smaller counts, and the cost model's choice
   if (err == hipSuccess && quads_serve(p, N)) {
-    std::vector<QuadCfg> quads{quad_shape(p, N)};
+    std::vector<QuadCfg> quads{quad_shape(p, B, C, N, false)};
     for (int k = 0; k < p->nquads; ++k)
       for (int w : {12, 9, 6, 3})
         if (w <= std::max(3, p->quads[k].nprogs)) quads.push_back(QuadCfg{k, w});
@@ -1062,7 +1063,7 @@ hipError_t launch_conv3x3(const sdnn_plan_s* p, const float* X, float* C, int32_
                           int32_t NB, const float* bias, int epi, hipStream_t stream) {
   const int32_t hwn[3] = {H, W, NB};
   if (quads_serve(p, H * W * NB))
-    return launch_quads(p, X, C, H * W * NB, bias, epi, hwn, quad_shape(p, H * W * NB), stream);
+    return launch_quads(p, X, C, H * W * NB, bias, epi, hwn, quad_shape(p, X, C, H * W * NB, true), stream);
   return launch_panels(p, X, C, H * W * NB, bias, epi, hwn, nullptr, nullptr, 0, stream);
 }
 

@@ -75,14 +75,10 @@ constexpr int kMaxQuadConsumers = 16 - kQuadProducers;
 struct QuadArgs {
   int32_t K, N, nchunks, nprogs;
   int32_t ring_chunks;  // chunk numbers an item takes up: nchunks, rounded up to half the ring
-  int32_t n_rb, n_tiles, total_wg, per_xcd, epi;
+  int32_t n_rb, n_tiles, total_wg, per_xcd, epi, cached;
   uint32_t poll_budget;
   int32_t H, W, NB;  // image geometry of a 3x3 convolution (B is then the input X)
 };
-
-// Staging kinds: 16-byte pieces and stores (N % 4 == 0, B and C 16-byte aligned), 4-byte ones
-// (any N), and the virtual B of a 3x3 convolution (16-byte pieces of an IC x H x W x NB input).
-enum { kQuadVec = 0, kQuadDword = 1, kQuadConv = 2 };
 
 // ---- producers --------------------------------------------------------------------------
 // (M0, the DMAs' LDS address, is not a register the compiler allocates; nothing else in these
@@ -292,7 +288,16 @@ __device__ __forceinline__ void produce(const float* B, const QuadArgs& a, int p
 // element, each element was a basic block of its own, whose reciprocal and exponential nothing
 // overlapped.  Lane group g of set q holds row q * kRows + g, the lane kVecs times four
 // columns (of groups of 4 lanes, the i-th vector is quarter i ^ (g % 4)).
-template <int NS, int STAGE, int EPI, int SETS, int ACCS>
+template <typename V, bool CACHED>
+__device__ __forceinline__ void store_vec(float* c, float x, float y, float z, float w) {
+  const nt_float4 v = {x, y, z, w};
+  if constexpr (CACHED) *reinterpret_cast<V*>(c) = v;
+  else __builtin_nontemporal_store(v, reinterpret_cast<V*>(c));
+}
+// (a 16-byte store needs 4-byte alignment only)
+typedef nt_float4 __attribute__((aligned(4))) dword_float4;
+
+template <int NS, int STAGE, int EPI, bool CACHED, int SETS, int ACCS>
 __device__ __forceinline__ void store_program(const group_acc_t<ACCS> (&acc)[SETS], const int (&out)[SETS],
                                               const float (&bb)[SETS], float* C, int n0, int lane, int N) {
   constexpr int kGroup = NS <= 2 ? 16 : 4, kVecs = ACCS / 4;
@@ -307,15 +312,32 @@ __device__ __forceinline__ void store_program(const group_acc_t<ACCS> (&acc)[SET
 #pragma unroll
     for (int i = 0; i < kVecs; ++i) {
       const int n = n0 + 4 * (lane % kGroup) + 4 * kGroup * (kVecs > 1 ? i ^ quarter : 0);
-      if (STAGE != kQuadDword) {
-        if (n < N) store_c4(c + n, v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]);
-      } else {
+      const float *e = v + 4 * i;
+      if constexpr (STAGE == kQuadDword) {
+        if (n + 4 <= N) {
+          store_vec<dword_float4, CACHED>(c + n, e[0], e[1], e[2], e[3]);
+        } else {
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
-          if (n + k < N) store_c1(c + n + k, v[4 * i + k]);
+          for (int k = 0; k < 3; ++k)
+            if (n + k < N) c[n + k] = e[k];
+        }
+      } else if (n < N) {
+        store_vec<nt_float4, CACHED>(c + n, e[0], e[1], e[2], e[3]);
       }
     }
   }
+}
+
+template <int NS, int STAGE, bool CACHED, int SETS, int ACCS>
+__device__ __forceinline__ void finish_program(const group_acc_t<ACCS> (&acc)[SETS], const int (&out)[SETS],
+                                               const float (&bb)[SETS], float* C, int n0, int lane,
+                                               const QuadArgs& a) {
+  if (a.epi == SDNN_EPI_GELU)
+    store_program<NS, STAGE, SDNN_EPI_GELU, CACHED>(acc, out, bb, C, n0, lane, a.N);
+  else if (a.epi == SDNN_EPI_RELU)
+    store_program<NS, STAGE, SDNN_EPI_RELU, CACHED>(acc, out, bb, C, n0, lane, a.N);
+  else
+    store_program<NS, STAGE, SDNN_EPI_NONE, CACHED>(acc, out, bb, C, n0, lane, a.N);
 }
 
 // A wave's place in its workgroup's items.
@@ -371,9 +393,10 @@ __device__ __forceinline__ void run_program(QuadConsumer& ca, bool entries, cons
       lds_write(ca.prog_addr, ca.next_progress);  // no entries: only epi(bias)
     }
     const int n0 = cur.tile * kQuadTileCols;
-    if (a.epi == SDNN_EPI_GELU) store_program<NS, STAGE, SDNN_EPI_GELU>(acc, out, bb, C, n0, lane, a.N);
-    else if (a.epi == SDNN_EPI_RELU) store_program<NS, STAGE, SDNN_EPI_RELU>(acc, out, bb, C, n0, lane, a.N);
-    else store_program<NS, STAGE, SDNN_EPI_NONE>(acc, out, bb, C, n0, lane, a.N);
+    if (a.cached)
+      finish_program<NS, STAGE, true>(acc, out, bb, C, n0, lane, a);
+    else
+      finish_program<NS, STAGE, false>(acc, out, bb, C, n0, lane, a);
     if (!cur.next(a)) return;
     cur.find(a);
   } while (cur.prog == prog);
@@ -481,6 +504,21 @@ hipError_t launch_stage(const DevQuads& d, const float* B, float* C, const float
   return hipErrorInvalidValue;
 }
 
+// Whether C is stored through the caches or streamed past them.  The groups of 4 lanes store 64
+// bytes of a row at a time.  Where rows of C do not begin at 64 bytes, those stores reach memory
+// as parts of lines unless L2 joins them first (3000 x 128 at 90 %, N = 3092: 29.6 us streamed,
+// 19.2 cached; N = 4095: 44.7 and 23.6; below 8 MB streaming is as fast or faster: 500 x 32,
+// N = 1000: 5.6 and 5.9).  Aligned ones are streamed (with three sets of B and C in turn, which
+// the 256 MB memory-side cache does not hold: 3072 x 768 at 97 %, N = 16384 96 us streamed, 123
+// cached; 768 x 768 32 and 39; 3000 x 96 49 and 57; a small C is written back when the kernel
+// ends: 256 x 256 9.3 and 10.4), but for a K so small that the store is all there is to do
+// (3000 x 32 at 90 %, N = 16384: 54 and 49).
+bool cached_stores(const sdnn_plan_s* p, const float* C, int32_t N) {
+  const int64_t bytes = (int64_t)p->M * N * 4;
+  if (N % 16 != 0 || ((uintptr_t)C & 63) != 0) return bytes >= (int64_t)8 << 20;
+  return p->K <= 32 && bytes >= (int64_t)48 << 20;
+}
+
 int env_or(const char* name, int dflt) {
   const char* s = getenv(name);
   return s ? atoi(s) : dflt;
@@ -489,30 +527,36 @@ int env_or(const char* name, int dflt) {
 // The packing and the consumer waves of a call: those that a cost model gives the least
 // time.  In microseconds, for a workgroup's item (all measured on MI355X):
 //     lat * (longest + mean program)/2 + thr * mean * max(waves / 4, 1)   blocks of 8 quad-steps
-//   + sync * chunks + 0.104 * ring chunks                                 handshakes, staging
-//   + store * rows                                                        epilogue
-// times the rounds of items over the CUs.  lat, thr, sync: 0.085, 0.036, 0.107 for programs
-// of 4 and 8 rows, 0.127, 0.011, 0.080 for those of 16 and 32; store: 0.0057, and 0.0083 for
-// 32-row programs.  Fitted to 4300 timings over 112 problems (M, K = 100 to 3072, 3 to 30 %
-// dense, N = 32 to 16384, uniform and lognormal rows): 10 % rms error, and the pick's time is
-// within 1.7 % of the fastest of the 44 candidates on average (22 % at worst, a 1500 x 100
-// layer at N = 16384).
-QuadCfg choose_quads(const sdnn_plan_s* p, int N) {
+//   + sync * chunks + stage * ring chunks                                 handshakes, staging
+//   + store * rows + item                                                 epilogue, start
+// times the rounds of items over the CUs.  lat, thr, sync, item: 0.073, 0.040, 0.147, 0.23 for
+// programs of 4 and 8 rows, 0.105, 0.015, 0.053, 0.26 (0.93) for those of 16 (32); stage: 0.13,
+// 4-byte pieces 0.20, a convolution 0.21; store: 0.0039 (32 rows 0.0033).  Fitted to 4900 timings
+// over 131 problems (M, K = 100 to 3072, 3 to 30 % dense, N = 32 to 16384, uniform and lognormal
+// rows, ragged N, convolutions): 9 % rms error.  Over 215 problems, those with K = 32 to 200
+// included, the pick's time is within 2 % of the fastest candidate's on average (20 % at worst),
+// the noise of the single timings included.  Programs of 32 rows, streamed, only from 8 chunks of
+// K up: below, their bursts of stores are what is waited for (1500 x 100 at 90 %, N = 16384: 34.8
+// against 30.8 us with 16-row ones).
+QuadCfg choose_quads(const sdnn_plan_s* p, int N, QuadStage stage, bool cached) {
   const int64_t tiles = (N + kQuadTileCols - 1) / kQuadTileCols;
   const int64_t cus = p->num_cus > 0 ? p->num_cus : 256;
   const int chunks = (p->K + kQuadChunk - 1) / kQuadChunk;
+  const double t_stage = stage == kQuadVec ? 0.13 : stage == kQuadDword ? 0.20 : 0.21;
   QuadCfg best{0, 1};
   double best_t = -1.0;
   for (int i = 0; i < p->nquads; ++i) {
     const DevQuads& d = p->quads[i];
-    const bool hex = d.cap >= 4;
+    if (d.cap == 8 && chunks < 8 && !cached) continue;
+    const bool wide = d.cap <= 2;
     const double mean = (double)d.blocks / d.nprogs;
-    const double lat = (hex ? 0.127 : 0.085) * 0.5 * (mean + d.longest) + (hex ? 0.080 : 0.107) * chunks;
+    const double fixed = (wide ? 0.073 : 0.105) * 0.5 * (mean + d.longest) +
+                         (wide ? 0.147 : 0.053) * chunks + (wide ? 0.23 : d.cap == 4 ? 0.26 : 0.93);
     for (int w = std::min(2, d.nprogs); w <= std::min(kMaxQuadConsumers, d.nprogs); ++w) {
       const int64_t items = tiles * ((d.nprogs + w - 1) / w), rounds = (items + cus - 1) / cus;
       const int staged = rounds > 1 ? (chunks + 3) / 4 * 4 : chunks;
-      const double t = rounds * (lat + (hex ? 0.011 : 0.036) * mean * std::max(0.25 * w, 1.0) +
-                                 0.104 * staged + (d.cap == 8 ? 0.0083 : 0.0057) * 4.0 * d.cap * w);
+      const double t = rounds * (fixed + (wide ? 0.040 : 0.015) * mean * std::max(0.25 * w, 1.0) +
+                                 t_stage * staged + (d.cap == 8 ? 0.0033 : 0.0039) * 4.0 * d.cap * w);
       if (best_t < 0.0 || t < best_t) {
         best_t = t;
         best = QuadCfg{i, w};
@@ -531,8 +575,12 @@ bool quads_serve(const sdnn_plan_s* p, int32_t N) {
          !getenv("SDNN_FORCE_TILE_MAJOR_WGS");
 }
 
-QuadCfg quad_shape(const sdnn_plan_s* p, int32_t N) {
-  QuadCfg c = choose_quads(p, N);
+static QuadStage quad_stage(const float* B, const float* C, int32_t N) {
+  return N % 4 == 0 && (((uintptr_t)B | (uintptr_t)C) & 15) == 0 ? kQuadVec : kQuadDword;
+}
+
+QuadCfg quad_shape(const sdnn_plan_s* p, const float* B, const float* C, int32_t N, bool conv) {
+  QuadCfg c = choose_quads(p, N, conv ? kQuadConv : quad_stage(B, C, N), cached_stores(p, C, N));
   const int cap = env_or("SDNN_FORCE_QUAD_CAP", 0), waves = env_or("SDNN_FORCE_QUAD_WAVES", 0);  // tests
   for (int i = 0; i < p->nquads; ++i)
     if (p->quads[i].cap == cap) c.pack = i;
@@ -555,6 +603,7 @@ hipError_t launch_quads(const sdnn_plan_s* p, const float* B, float* C, int32_t 
   args.n_rb = (d.nprogs + waves - 1) / waves;
   args.n_tiles = (N + kQuadTileCols - 1) / kQuadTileCols;
   args.epi = epi;
+  args.cached = cached_stores(p, C, N);
   const int64_t items = (int64_t)args.n_rb * args.n_tiles;
   if (items > (int64_t)1 << 30) return hipErrorInvalidValue;
   args.total_wg = (int32_t)std::min(items, cus);
@@ -566,8 +615,8 @@ hipError_t launch_quads(const sdnn_plan_s* p, const float* B, float* C, int32_t 
   args.NB = conv_hwn ? conv_hwn[2] : 0;
   const int grid = args.per_xcd * 8;
   if (conv_hwn) return launch_stage<kQuadConv>(d, B, C, bias, args, waves, grid, stream);
-  const bool vec = N % 4 == 0 && (((uintptr_t)B | (uintptr_t)C) & 15) == 0;
-  return vec ? launch_stage<kQuadVec>(d, B, C, bias, args, waves, grid, stream)
+  return quad_stage(B, C, N) == kQuadVec
+             ? launch_stage<kQuadVec>(d, B, C, bias, args, waves, grid, stream)
              : launch_stage<kQuadDword>(d, B, C, bias, args, waves, grid, stream);
 }
 

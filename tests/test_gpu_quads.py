@@ -159,3 +159,17 @@ def test_convolution(force, cap, OC, IC, H, W, NB):
     ref, bound = oracle.conv3x3_f64(L.F.row_ptr, L.F.col_idx, L.F.values, L.X, L.bias, "relu")
     assert (np.abs(out[0].astype(np.float64) - ref) <= tol_fp32(bound, "relu")).all()
     assert np.array_equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("cap", [2, 4, 8])
+@pytest.mark.parametrize("M,K,N,density", [
+    (700, 40, 3092, 0.2), (700, 40, 3001, 0.2),   # rows of C off 64 bytes, past 8 MB
+    (160, 70, 1003, 0.3),                         # the same, below it
+    (800, 32, 16384, 0.2), (800, 33, 16384, 0.2),  # aligned rows past 48 MB, K of 32 and above
+])
+def test_output_stores(force, cap, M, K, N, density):
+    """Both sides of the rule that stores C through the caches or streams it, with 16-byte
+    stores to rows that are 16- and 4-byte aligned."""
+    force(cap, 12)
+    W = inputs.pattern_uniform(M, K, density, inputs.CFG_TEST, 7300 + M + K, 0.05)
+    check(W, N, f"stores cap {cap} M {M} K {K}")
