@@ -63,9 +63,9 @@ typedef enum {
  *                 panels for 128-column tiles unless tile_cols = 256; with tile_cols = 0
  *                 too (a default plan), also for the row-quad kernel, which then serves
  *                 sdnn_spmm and sdnn_conv3x3 (same result bit for bit; products unless
- *                 sdnn_plan_tune measured the panel kernel faster at N).  The panel kernel, which serves the K-split
- *                 calls and plans that fix panel_rows or tile_cols, picks one packing per
- *                 call: the 32-row panels (with 12 consumer waves per workgroup) when W
+ *                 sdnn_plan_tune measured the panel kernel faster at N).  The panel
+ *                 kernel, which serves the K-split calls and plans that fix panel_rows or
+ *                 tile_cols, picks one packing per call: the 32-row panels (with 12 consumer waves per workgroup) when W
  *                 holds under 20 entries per 16 rows and 32 columns and their grid fills
  *                 the compute units; otherwise the fewest rounds of workgroups over the
  *                 compute units, then the most units busy, then the shortest panels
