@@ -65,13 +65,14 @@ typedef enum {
  *                 sdnn_spmm and sdnn_conv3x3 (same result bit for bit; products unless
  *                 sdnn_plan_tune measured the panel kernel faster at N).  The panel
  *                 kernel, which serves the K-split calls and plans that fix panel_rows or
- *                 tile_cols, picks one packing per call: the 32-row panels (with 12 consumer waves per workgroup) when W
- *                 holds under 20 entries per 16 rows and 32 columns and their grid fills
- *                 the compute units; otherwise the fewest rounds of workgroups over the
- *                 compute units, then the most units busy, then the shortest panels
- *                 averaging at least 8 entries per 32 columns of W (4-row panels are not
- *                 used below 8); sdnn_plan_tune can replace that choice by a timed one,
- *                 and sdnn_plan_launch_shape reports it.  4, 8, 12 or 16 packs that
+ *                 tile_cols, picks one packing per call: the 32-row panels (with 12
+ *                 consumer waves per workgroup) when W holds under 20 entries per 16 rows
+ *                 and 32 columns and their grid fills the compute units; otherwise the
+ *                 fewest rounds of workgroups over the compute units, then the most units
+ *                 busy, then the shortest panels averaging at least 8 entries per 32
+ *                 columns of W (4-row panels are not used below 8); sdnn_plan_tune can
+ *                 replace that choice by a timed one, and sdnn_plan_launch_shape reports
+ *                 it. 4, 8, 12 or 16 packs that
  *                 height only; 32 too, with tile_cols = 128 (else SDNN_ERR_DIM).
  *   permute:      1 = apply Algorithm 1 (default), 0 = identity order (ablation),
  *                 2 = panel-balancing order: rows, by nonzero count descending, each
