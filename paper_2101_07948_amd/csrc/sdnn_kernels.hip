@@ -888,7 +888,9 @@ hipError_t launch_spmm(const sdnn_plan_s* p, const float* B, float* C, int32_t N
 hipError_t launch_spmm_split(const sdnn_plan_s* p, const float* B, float* C, int32_t N,
                              const float* bias, int epi, int splits, float* ws,
                              hipStream_t stream) {
-  if (split_runs_of(p, N, splits, false, nullptr) == 1) return launch_spmm(p, B, C, N, bias, epi, stream);
+  const int nk = split_runs_of(p, N, splits, false, nullptr);
+  if (nk == 1) return launch_spmm(p, B, C, N, bias, epi, stream);
+  if (p->ntuned == 0) splits = nk;  // (a tuned count of its own comes with its tile width)
   return launch_panels(p, B, C, N, bias, epi, nullptr, nullptr, ws, splits, stream);
 }
 
@@ -1071,9 +1073,10 @@ hipError_t launch_conv3x3_split(const sdnn_plan_s* p, const float* X, float* C, 
                                 int32_t W, int32_t NB, const float* bias, int epi, int splits,
                                 float* ws, hipStream_t stream) {
   const int32_t hwn[3] = {H, W, NB};
-  if (split_runs_of(p, H * W * NB, splits, true, nullptr) == 1)
-    return launch_conv3x3(p, X, C, H, W, NB, bias, epi, stream);
-  return launch_panels(p, X, C, H * W * NB, bias, epi, hwn, nullptr, ws, splits, stream);
+  // the count is handed on, so that the model runs once per call
+  const int nk = split_runs_of(p, H * W * NB, splits, true, nullptr);
+  if (nk == 1) return launch_conv3x3(p, X, C, H, W, NB, bias, epi, stream);
+  return launch_panels(p, X, C, H * W * NB, bias, epi, hwn, nullptr, ws, nk, stream);
 }
 
 // ---------------------------------------------------------------------------------

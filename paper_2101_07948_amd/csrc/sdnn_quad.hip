@@ -540,7 +540,7 @@ int env_or(const char* name, int dflt) {
 // against 30.8 us with 16-row ones).
 QuadCfg choose_quads(const sdnn_plan_s* p, int N, QuadStage stage, bool cached) {
   const int64_t tiles = (N + kQuadTileCols - 1) / kQuadTileCols;
-  const int64_t cus = p->num_cus > 0 ? p->num_cus : 256;
+  const uint32_t cus = p->num_cus > 0 ? p->num_cus : 256;
   const int chunks = (p->K + kQuadChunk - 1) / kQuadChunk;
   const double t_stage = stage == kQuadVec ? 0.13 : stage == kQuadDword ? 0.20 : 0.21;
   QuadCfg best{0, 1};
@@ -553,7 +553,9 @@ QuadCfg choose_quads(const sdnn_plan_s* p, int N, QuadStage stage, bool cached) 
     const double fixed = (wide ? 0.073 : 0.105) * 0.5 * (mean + d.longest) +
                          (wide ? 0.147 : 0.053) * chunks + (wide ? 0.23 : d.cap == 4 ? 0.26 : 0.93);
     for (int w = std::min(2, d.nprogs); w <= std::min(kMaxQuadConsumers, d.nprogs); ++w) {
-      const int64_t items = tiles * ((d.nprogs + w - 1) / w), rounds = (items + cus - 1) / cus;
+      const int64_t items = tiles * ((d.nprogs + w - 1) / w);
+      // (the loop is host time of every call: 32-bit divisions where they do)
+      const int64_t rounds = items < (int64_t)1 << 31 ? ((uint32_t)items + cus - 1) / cus : (items + cus - 1) / cus;
       const int staged = rounds > 1 ? (chunks + 3) / 4 * 4 : chunks;
       const double t = rounds * (fixed + (wide ? 0.040 : 0.015) * mean * std::max(0.25 * w, 1.0) +
                                  t_stage * staged + (d.cap == 8 ? 0.0033 : 0.0039) * 4.0 * d.cap * w);
