@@ -43,7 +43,8 @@ groups of 16) after the reads it needs have landed (LDS returns in order, so lgk
 down through them); load block g + 4 into block g's register.  The loads run up to
 kQuadTailBlocks blocks past a program's end; the stream carries as many at its end.
 A wait is bounded by the poll budget; a wave that went on without waiting, or whose chunks a
-producer may have overwritten, leaves NaN.
+producer may have overwritten, leaves the NaN POISON in every accumulator, by which the epilogue
+knows it.
 """
 import os
 import sys
@@ -59,6 +60,7 @@ NE = 4
 VB = (32, 64)
 ACC = 96
 HISHIFT, LOSHIFT, NBITS = 19, 6, 6
+POISON = 0x7FC0DEAD
 NMASK = (1 << NBITS) - 1
 NSETS = (1, 2, 4, 8)
 # SGPRs
@@ -223,7 +225,7 @@ def consumer(ns):
           ".L%=_poison:"]
     per = 4 if ns <= 2 else 16                      # accumulators per set
     sets = ns if ns <= 2 else ns // 4
-    L += [f"v_mov_b32 v{ACC + x}, 0x7fc00000" for x in range(per * sets)]
+    L += [f"v_mov_b32 v{ACC + x}, {hex(POISON)}" for x in range(per * sets)]
     L += [".L%=_clean:", "v_mov_b32 v30, %[next]"]
     L += lane0_write("%[pa]", "v30")
     L.append("s_waitcnt vmcnt(0) lgkmcnt(0)")
@@ -251,7 +253,7 @@ def generate() -> str:
              f"constexpr int kQuadAsmTailBlocks = {NE + 1};",
              f"constexpr int kQuadAsmUnits = {UNITS}, kQuadAsmAccBase = {ACC};",
              f"constexpr int kQuadAsmLoShift = {LOSHIFT}, kQuadAsmHiShift = {HISHIFT};",
-             f"constexpr uint32_t kQuadAsmCountMask = {hex(NMASK)}u;", ""]
+             f"constexpr uint32_t kQuadAsmCountMask = {hex(NMASK)}u, kQuadAsmPoison = {hex(POISON)}u;", ""]
     parts += [consumer(ns) for ns in NSETS]
     return "\n".join(parts)
 

@@ -34,7 +34,8 @@ a per-wave poll budget (a launch argument), after which the wave goes on without
 waiting, so the kernel always ends.  Going on is never silent: a producer that stages
 past the ring limit first sets the workgroup's overrun word, and a consumer whose
 budget ran out, or that finds the overrun word set when it finishes, replaces its
-whole panel's results with NaN.
+whole panel's results with the NaN POISON, by which the epilogue (or, of a K-split call, the
+reduction) knows them.
 
 Stream consumed (see sdnn_internal.h): per panel, groups of 16 dwords (64 bytes,
 one scalar load, one scalar-cache line) [w0..w7 a0..a7]; w = fp32 weight bits;
@@ -93,6 +94,7 @@ PMAX_VEC, PMAX_DWORD = 2, 1                   # chunks in flight per producer va
 TOUCH_AHEAD = 512  # bytes of stream pulled into L2 ahead of the scalar ring
 GROUP_BYTES = 8 * G
 INF = 0x7FFFFFFF
+POISON = 0x7FC0DEAD
 MAX_CONS = 14      # consumer waves a workgroup can have
 PROFILE = False    # scratch builds only: time consumers spend waiting (%[twait])
 
@@ -295,7 +297,7 @@ def consumer(rw, limit=False, lay=WIDE):
           f"v_readfirstlane_b32 s{STMP}, v30",
           f"s_cmp_eq_u32 s{STMP}, 0", "s_cbranch_scc1 .L%=_clean",
           ".L%=_poison:"]
-    L += [f"v_mov_b32 v{ACC + x}, 0x7fc00000" for x in range(V * rw)]
+    L += [f"v_mov_b32 v{ACC + x}, {hex(POISON)}" for x in range(V * rw)]
     L += [".L%=_clean:", "v_mov_b32 v30, %[next]"]
     L += lane0_write("%[pa]", "v30", lay)
     L += ["s_waitcnt vmcnt(0) lgkmcnt(0)", f"s_mov_b32 m0, s{M0S}"]
@@ -745,7 +747,7 @@ def generate() -> str:
              f"constexpr int kAsmProducersN = {NARROW.NPROD}, kAsmTileBytesN = {NARROW.ROW_BYTES};",
              f"constexpr int kAsmAccBaseN = {NARROW.ACC}, kAsmEndBitN = {NARROW.END_BIT};",
              f"constexpr uint32_t kAsmRingMaskN = {hex(NARROW.RING_MASK)}u;",
-             f"constexpr uint32_t kProgressDone = {hex(INF)}u;",
+             f"constexpr uint32_t kProgressDone = {hex(INF)}u, kAsmPoison = {hex(POISON)}u;",
              ""]
     for rw in RW_VARIANTS:
         parts.append(consumer(rw))

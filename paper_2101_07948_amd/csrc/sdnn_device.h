@@ -60,6 +60,15 @@ __device__ __forceinline__ float activation(float x, int epi) {
   return x;
 }
 
+// What a consumer wave leaves in all of its accumulators when it went on without waiting, or
+// its chunks may have been overwritten: a NaN whose payload no arithmetic makes.  Its rows are
+// stored as NaN whatever the activation is (fmaxf(NaN, 0) = 0: a ReLU would otherwise turn the
+// rows into plausible zeros).  The value is the same in every accumulator, so one is looked at.
+constexpr uint32_t kPoison = 0x7fc0deadu;
+__device__ __forceinline__ int epilogue_of(float acc, int epi) {  // of a wave
+  return (uint32_t)__builtin_amdgcn_readfirstlane(__float_as_int(acc)) == kPoison ? (int)SDNN_EPI_NONE : epi;
+}
+
 }  // namespace
 }  // namespace sdnn
 

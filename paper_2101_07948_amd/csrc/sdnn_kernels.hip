@@ -148,6 +148,7 @@ constexpr int kCtlWords = 256;
 static_assert(512 + 16 * kProducers <= kCtlWords * 4, "filler words outside the control area");
 static_assert(kAsmProducersN <= kProducers, "ready words overlap the progress words");
 static_assert(kProducers <= 16, "ready words overlap the progress words");
+static_assert(kAsmPoison == kPoison, "poison mismatch");
 
 // Scalar launch parameters (the pointers are separate __restrict__ kernel arguments so
 // the compiler may read them through the scalar cache).
@@ -354,6 +355,7 @@ __global__ __launch_bounds__((threads_of<RW, TW>()), (min_waves_of<RW, TW>())) v
       ctl[16 + wave] = next;  // nothing to read in this row-block
     }
 
+    const int epi = epilogue_of(p0[0], a.epi);
 #pragma unroll
     for (int r = 0; r < RW; ++r) {
       const int orig = panel_rows[panel * RW + r];
@@ -370,9 +372,9 @@ __global__ __launch_bounds__((threads_of<RW, TW>()), (min_waves_of<RW, TW>())) v
         const float bb = bias ? bias[orig] : 0.0f;
         float* crow = C + (size_t)row * a.N;
         if (ncol + 2 <= a.N) {
-          store_c2(crow + ncol, activation(v[0] + bb, a.epi), activation(v[1] + bb, a.epi));
+          store_c2(crow + ncol, activation(v[0] + bb, epi), activation(v[1] + bb, epi));
         } else if (ncol < a.N) {
-          store_c1(crow + ncol, activation(v[0] + bb, a.epi));
+          store_c1(crow + ncol, activation(v[0] + bb, epi));
         }
         continue;
       }
@@ -390,12 +392,12 @@ __global__ __launch_bounds__((threads_of<RW, TW>()), (min_waves_of<RW, TW>())) v
       const float bb = bias ? bias[orig] : 0.0f;
       float* crow = C + (size_t)row * a.N;
       if (STAGE != kStageDword && ncol + 4 <= a.N) {
-        store_c4(crow + ncol, activation(v[0] + bb, a.epi), activation(v[1] + bb, a.epi),
-                 activation(v[2] + bb, a.epi), activation(v[3] + bb, a.epi));
+        store_c4(crow + ncol, activation(v[0] + bb, epi), activation(v[1] + bb, epi),
+                 activation(v[2] + bb, epi), activation(v[3] + bb, epi));
       } else {
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-          if (ncol + i < a.N) store_c1(crow + ncol + i, activation(v[i] + bb, a.epi));
+          if (ncol + i < a.N) store_c1(crow + ncol + i, activation(v[i] + bb, epi));
       }
     }
   }
@@ -656,20 +658,28 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
     const float bb = bias ? bias[rowmap ? rowmap[i] : i] : 0.0f;
     if (VEC) {
       float4 acc = *reinterpret_cast<const float4*>(ws + at);
+      bool spent = __float_as_uint(acc.x) == kPoison;  // (a wave's columns come in fours)
       for (int s = 1; s < nseg; ++s) {
         const float4 v = *reinterpret_cast<const float4*>(ws + s * plane + at);
+        spent |= __float_as_uint(v.x) == kPoison;
         acc.x += v.x;
         acc.y += v.y;
         acc.z += v.z;
         acc.w += v.w;
       }
-      store_c4(C + at, activation(acc.x + bb, epi), activation(acc.y + bb, epi),
-               activation(acc.z + bb, epi), activation(acc.w + bb, epi));
+      const int act = spent ? (int)SDNN_EPI_NONE : epi;  // (the sums are NaN)
+      store_c4(C + at, activation(acc.x + bb, act), activation(acc.y + bb, act),
+               activation(acc.z + bb, act), activation(acc.w + bb, act));
     } else {
       for (int c = 0; c < 4 && n + c < N; ++c) {
         float acc = ws[at + c];
-        for (int s = 1; s < nseg; ++s) acc += ws[s * plane + at + c];
-        store_c1(C + at + c, activation(acc + bb, epi));
+        bool spent = __float_as_uint(acc) == kPoison;
+        for (int s = 1; s < nseg; ++s) {
+          const float v = ws[s * plane + at + c];
+          spent |= __float_as_uint(v) == kPoison;
+          acc += v;
+        }
+        store_c1(C + at + c, activation(acc + bb, spent ? (int)SDNN_EPI_NONE : epi));
       }
     }
   }

@@ -62,6 +62,7 @@ static_assert(kQuadAsmUnits == kQuadUnits, "block layout mismatch");
 static_assert(kQuadAsmLoShift == kQuadLoShift && kQuadAsmHiShift == kQuadHiShift &&
                   kQuadAsmCountMask == kQuadMaxBlocks,
               "descriptor fields mismatch");
+static_assert(kQuadAsmPoison == kPoison, "poison mismatch");
 
 constexpr uint32_t kProgressEnd = 0x7fffffffu;
 constexpr int kPollBudgetQuad = 1 << 22;
@@ -332,9 +333,10 @@ template <int NS, int STAGE, bool CACHED, int SETS, int ACCS>
 __device__ __forceinline__ void finish_program(const group_acc_t<ACCS> (&acc)[SETS], const int (&out)[SETS],
                                                const float (&bb)[SETS], float* C, int n0, int lane,
                                                const QuadArgs& a) {
-  if (a.epi == SDNN_EPI_GELU)
+  const int epi = epilogue_of(acc[0][0], a.epi);
+  if (epi == SDNN_EPI_GELU)
     store_program<NS, STAGE, SDNN_EPI_GELU, CACHED>(acc, out, bb, C, n0, lane, a.N);
-  else if (a.epi == SDNN_EPI_RELU)
+  else if (epi == SDNN_EPI_RELU)
     store_program<NS, STAGE, SDNN_EPI_RELU, CACHED>(acc, out, bb, C, n0, lane, a.N);
   else
     store_program<NS, STAGE, SDNN_EPI_NONE, CACHED>(acc, out, bb, C, n0, lane, a.N);

@@ -161,6 +161,68 @@ def test_convolution(force, cap, OC, IC, H, W, NB):
     assert np.array_equal(out[0], out[1])
 
 
+def spent(call, ref, tol, budget):
+    """A call with every wait's budget forced to a few polls: within the bar or NaN, and NaN
+    everywhere without any."""
+    old = os.environ.get("SDNN_POLL_BUDGET")
+    os.environ["SDNN_POLL_BUDGET"] = str(budget)
+    try:
+        got = call()
+    finally:
+        if old is None:
+            os.environ.pop("SDNN_POLL_BUDGET")
+        else:
+            os.environ["SDNN_POLL_BUDGET"] = old
+    ok = (np.abs(got.astype(np.float64) - ref) <= tol) | np.isnan(got)
+    assert ok.all(), f"{int((~ok).sum())} finite outputs out of tolerance"
+    assert budget > 0 or np.isnan(got).all()
+
+
+@pytest.mark.parametrize("budget", [0, 3])
+@pytest.mark.parametrize("epi", ["none", "relu", "gelu"])
+@pytest.mark.parametrize("cap", [1, 2, 4, 8])
+def test_spent_budget_is_nan_after_any_activation(force, cap, epi, budget):
+    """A wave that stops waiting stores NaN whatever the activation: 16- and 4-byte staging (N of
+    1024 and 1023), several items per workgroup, and a convolution."""
+    force(cap, 4)
+    print(f"spent budget {budget} cap {cap} {epi}", flush=True)
+    W = inputs.pattern_uniform(300, 700, 0.1, inputs.CFG_TEST, 7700, 0.05)
+    bias = inputs.bias_normal(300, inputs.CFG_TEST, 7701, 0.02)
+    for N in (1024, 1023, 8192):
+        B = inputs.dense_B(700, N, inputs.CFG_TEST, 7702)
+        ref, bound = oracle.spmm_f64(W.row_ptr, W.col_idx, W.values, 700, B, bias, epi)
+        with sd.Plan.from_csr(W) as plan:
+            spent(lambda: run(plan, torch.from_numpy(B).to(DEV), bias, epi), ref, tol_fp32(bound, epi), budget)
+    L = inputs.conv_layer(40, 64, 9, 9, 8, 0.6, layer=770, epi=epi)
+    ref, bound = oracle.conv3x3_f64(L.F.row_ptr, L.F.col_idx, L.F.values, L.X, L.bias, epi)
+    with sd.Plan.from_csr(L.F) as plan:
+        def conv():
+            C = torch.full((40, 9, 9, 8), float("nan"), device=DEV)
+            plan.conv3x3(torch.from_numpy(L.X).to(DEV), C, torch.from_numpy(L.bias).to(DEV), epi)
+            torch.cuda.synchronize()
+            return C.cpu().numpy()
+        spent(conv, ref, tol_fp32(bound, epi), budget)
+
+
+@pytest.mark.parametrize("N", [1024, 1023])
+@pytest.mark.parametrize("tile_cols", [128, 256])
+def test_spent_budget_is_nan_after_relu_on_the_panel_kernel(N, tile_cols):
+    """The same of the panel kernel, unsplit and on runs of K, whose reduction applies the ReLU."""
+    W = inputs.pattern_uniform(300, 700, 0.1, inputs.CFG_TEST, 7710, 0.05)
+    B = inputs.dense_B(700, N, inputs.CFG_TEST, 7711)
+    ref, bound = oracle.spmm_f64(W.row_ptr, W.col_idx, W.values, 700, B, None, "relu")
+    Bt = torch.from_numpy(B).to(DEV)
+    with sd.Plan.from_csr(W, tile_cols=tile_cols, split_chunks=4) as plan:
+        def split():
+            C = torch.zeros(300, N, device=DEV)
+            plan.spmm_split(Bt, C, None, "relu", splits=3)
+            torch.cuda.synchronize()
+            return C.cpu().numpy()
+        for budget in (0, 3):
+            spent(lambda: run(plan, Bt, None, "relu"), ref, tol_fp32(bound, "relu"), budget)
+            spent(split, ref, tol_fp32(bound, "relu"), budget)
+
+
 @pytest.mark.parametrize("cap", [2, 4, 8])
 @pytest.mark.parametrize("M,K,N,density", [
     (700, 40, 3092, 0.2), (700, 40, 3001, 0.2),   # rows of C off 64 bytes, past 8 MB
