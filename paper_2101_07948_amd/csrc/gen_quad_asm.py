@@ -108,7 +108,9 @@ def fmas(e, vb, ns, last=False):
         acc = ACC + 16 * (u if ns == 8 else 0)
         for i in range(4):
             if not last:
-                L.append(f"s_waitcnt lgkmcnt({15 - (4 * u + i)})")
+                # (16 or 17 LDS instructions are in flight before the first wait: a 4-bit counter
+                # at its end stands for 15 or more, so no wait is on 15)
+                L.append(f"s_waitcnt lgkmcnt({min(14, 15 - (4 * u + i))})")
             for k in range(4):
                 L.append(f"v_fmac_f32 v{acc + 4 * i + k}, v{WREG[u]}, v{vb + 16 * u + 4 * i + k}")
     return L

@@ -1,11 +1,14 @@
 """Host self-check of the row-quad packings (sdnn_plan_check_host re-walks every program of a
 default plan: each entry once, in its row, in ascending column order, with its weight bits and
 inside the chunks its descriptor states)."""
+import os
+import re
+
 import numpy as np
 import pytest
 
 import paper_2101_07948_amd as sd
-from conftest import random_csr
+from conftest import ROOT, random_csr
 
 
 def check(row_ptr, col_idx, values, M, K, **kw):
@@ -33,3 +36,13 @@ def test_empty_and_extreme_rows():
     cols = np.concatenate([lo, hi, lo, hi, np.arange(0, K, 70)]).astype(np.int32)
     rp = np.cumsum([0, 300, 300, 300, 300, len(range(0, K, 70))]).astype(np.int32)
     check(rp, cols, np.ones(len(cols), np.float32), 5, K)
+
+
+def test_no_wait_on_a_counter_at_its_end():
+    """The LDS counter has 4 bits: at 15 it may stand for more, and a wait for "at most 15 in flight"
+    waits for nothing.  Every wait of the generated loops is on 14 or fewer (the loads' counter,
+    of 6 bits, on 62 or fewer)."""
+    text = open(os.path.join(ROOT, "paper_2101_07948_amd", "csrc", "quad_asm_gen.h")).read()
+    lds = [int(n) for n in re.findall(r"lgkmcnt\((\d+)\)", text)]
+    loads = [int(n) for n in re.findall(r"vmcnt\((\d+)\)", text)]
+    assert lds and max(lds) <= 14 and loads and max(loads) <= 62
