@@ -42,7 +42,7 @@ ds_reads of block g + 1; the FMAs of block g, each quarter of a unit (or the who
 groups of 16) after the reads it needs have landed (LDS returns in order, so lgkmcnt counts
 down through them); load block g + 4 into block g's register.  The loads run up to
 kQuadTailBlocks blocks past a program's end; the stream carries as many at its end.
-A wait is bounded by the poll budget; a wave that went on without waiting, or whose chunks a
+A wave's waits are bounded by its poll budget, over all the items it runs; a wave that went on without waiting, or whose chunks a
 producer may have overwritten, leaves the NaN POISON in every accumulator, by which the epilogue
 knows it.
 """
@@ -230,19 +230,19 @@ def consumer(ns):
     L += [f"v_mov_b32 v{ACC + x}, {hex(POISON)}" for x in range(per * sets)]
     L += [".L%=_clean:", "v_mov_b32 v30, %[next]"]
     L += lane0_write("%[pa]", "v30")
-    L.append("s_waitcnt vmcnt(0) lgkmcnt(0)")
+    L += [f"s_mov_b32 %[budget], s{SPOLL}", "s_waitcnt vmcnt(0) lgkmcnt(0)"]
     body = "\n".join('      "' + x + '\\n\\t"' for x in L)
     accs = ", ".join(f'"+{{v[{ACC + per * q}:{ACC + per * (q + 1) - 1}]}}"(acc[{q}])' for q in range(sets))
     regs = [f"s{x}" for x in range(PTR, SHI + 1)] + [f"v{x}" for x in range(EREG, ACC)]
     clob = ", ".join(f'"{r}"' for r in regs + ["scc", "memory"])
     return f"""// Consumer, {4 * ns} rows per wave
-__device__ __forceinline__ void consume_quads{ns}(group_acc_t<{per}> (&acc)[{sets}], const QuadConsumer& a) {{
+__device__ __forceinline__ void consume_quads{ns}(group_acc_t<{per}> (&acc)[{sets}], QuadConsumer& a) {{
   asm volatile(
 {body}
-      : {accs}
+      : {accs}, [budget] "+s"(a.poll_budget)
       : [sp] "s"(a.stream), [dp] "s"(a.descs), [vl] "v"(a.vlane), [l4] "v"(a.lane4),
         [pa] "v"(a.prog_addr), [ra] "v"(a.ready_addr), [ov] "v"(a.overrun_addr),
-        [budget] "s"(a.poll_budget), [cbase] "s"(a.chunk_base), [next] "s"(a.next_progress)
+        [cbase] "s"(a.chunk_base), [next] "s"(a.next_progress)
       : {clob});
 }}
 """

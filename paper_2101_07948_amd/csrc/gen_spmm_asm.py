@@ -300,7 +300,7 @@ def consumer(rw, limit=False, lay=WIDE):
     L += [f"v_mov_b32 v{ACC + x}, {hex(POISON)}" for x in range(V * rw)]
     L += [".L%=_clean:", "v_mov_b32 v30, %[next]"]
     L += lane0_write("%[pa]", "v30", lay)
-    L += ["s_waitcnt vmcnt(0) lgkmcnt(0)", f"s_mov_b32 m0, s{M0S}"]
+    L += ["s_waitcnt vmcnt(0) lgkmcnt(0)", f"s_mov_b32 %[budget], s{SPOLL}", f"s_mov_b32 m0, s{M0S}"]
     body = "\n".join('      "' + x + '\\n\\t"' for x in L)
     planes = ", ".join(f'"+{{v[{ACC + k * rw}:{ACC + k * rw + rw - 1}]}}"(p{k})' for k in range(V))
     lo, hi = min(E[0], PTR), max(E[-1] + 2 * G - 1, lay.SREADY1)
@@ -310,16 +310,16 @@ def consumer(rw, limit=False, lay=WIDE):
     clob = ", ".join(f'"{r}"' for r in sregs + vregs + ["scc", "memory"])
     name = f"consume_{lay.prefix}rw{rw}" + ("_limit" if limit else "")
     operands = ('[sp] "s"(a.stream), [vl] "v"(a.vlane), [pa] "v"(a.prog_addr), '
-                '[ra] "v"(a.ready_addr),\n        [budget] "s"(a.poll_budget), '
+                '[ra] "v"(a.ready_addr),\n        '
                 '[ov] "v"(a.overrun_addr), [cbase] "s"(a.chunk_base), [next] "s"(a.next_progress)'
                 + (', [climit] "s"(a.chunk_limit)' if limit else ''))
     params = ", ".join(f"acc_plane_t<{rw}>& p{k}" for k in range(V))
     return f"""// Consumer, RW = {rw}, {64 * V}-column tiles{', stopping at the chunk limit' if limit else ''}: accumulator planes p0..p{V - 1}
 __device__ __forceinline__ void {name}({params},
-    {'' if PROFILE else 'const '}ConsumerArgs& a) {{
+    ConsumerArgs& a) {{
   asm volatile(
 {body}
-      : {planes}{', [twait] "=&s"(a.twait)' if PROFILE else ''}
+      : {planes}, [budget] "+s"(a.poll_budget){', [twait] "=&s"(a.twait)' if PROFILE else ''}
       : {operands}
       : {clob});
 }}

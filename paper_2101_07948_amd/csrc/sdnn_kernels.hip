@@ -56,7 +56,7 @@ struct ConsumerArgs {
   uint32_t vlane;          // 16 * lane: the lane's byte offset in a staged B row
   uint32_t prog_addr;      // LDS address of this consumer's progress word
   uint32_t ready_addr;     // LDS address of the ready word
-  uint32_t poll_budget;    // failed readiness checks the wave may poll through in total
+  uint32_t poll_budget;    // failed readiness checks the wave may still poll through (all items)
   uint32_t overrun_addr;   // LDS address of the workgroup's overrun word
   uint32_t chunk_limit;    // the wave stops before a sync group whose c_lo reaches this chunk
   uint32_t chunk_base;     // ring chunk number of the item's chunk 0 (added to c_lo, c_hi)
@@ -290,6 +290,7 @@ __global__ __launch_bounds__((threads_of<RW, TW>()), (min_waves_of<RW, TW>())) v
     return;
   }
 
+  uint32_t budget = a.poll_budget;
   for (int it = 0; it < nitems; ++it) {
     int tile = tile0, rb = g + it * a.wg_per_tile;
     if (a.tile_major) {
@@ -321,7 +322,7 @@ __global__ __launch_bounds__((threads_of<RW, TW>()), (min_waves_of<RW, TW>())) v
       ca.vlane = (uint32_t)lane * (4u * V);
       ca.prog_addr = prog0 + 4u * (uint32_t)wave;
       ca.ready_addr = ready_addr;
-      ca.poll_budget = a.poll_budget;
+      ca.poll_budget = budget;
       ca.overrun_addr = overrun_addr;
       ca.chunk_limit = (uint32_t)c1;
       ca.chunk_base = cbase;
@@ -351,6 +352,7 @@ __global__ __launch_bounds__((threads_of<RW, TW>()), (min_waves_of<RW, TW>())) v
         if constexpr (RW == 12) consume_rw12(p0, p1, p2, p3, ca);
         if constexpr (RW == 16) consume_rw16(p0, p1, p2, p3, ca);
       }
+      budget = ca.poll_budget;
     } else if (lane == 0) {
       ctl[16 + wave] = next;  // nothing to read in this row-block
     }

@@ -51,7 +51,7 @@ struct QuadConsumer {
   uint32_t prog_addr;      // LDS address of this consumer's progress word
   uint32_t ready_addr;     // LDS address of the ready words
   uint32_t overrun_addr;   // LDS address of the workgroup's overrun word
-  uint32_t poll_budget;    // failed readiness checks the wave may poll through in total
+  uint32_t poll_budget;    // failed readiness checks the wave may still poll through (all items)
   uint32_t chunk_base;     // ring chunk number of the item's chunk 0
   uint32_t next_progress;  // progress word written when the program is done
 };
@@ -460,6 +460,7 @@ __global__ __launch_bounds__(1024) void spmm_quad_kernel(
   cur.item = lin;
   cur.stratum = (g4 & 1) && 4 * g4 + 4 <= nc ? 4 * g4 + 3 - i4 : wave;
   cur.find(a);
+  uint32_t budget = a.poll_budget;
   while (cur.it < nitems) {
     if (cur.prog >= a.nprogs) {  // no program in this row-block
       if (lane == 0)
@@ -476,13 +477,14 @@ __global__ __launch_bounds__(1024) void spmm_quad_kernel(
     ca.prog_addr = progress;
     ca.ready_addr = kCtl;
     ca.overrun_addr = kCtl + 128u;
-    ca.poll_budget = a.poll_budget;
+    ca.poll_budget = budget;
     const int32_t* r = rows + (size_t)cur.prog * (4 * CAP);
     const int32_t* o = outs + (size_t)cur.prog * (4 * CAP);
     if (CAP == 8 && P.NS == 8) run_program<8, STAGE>(ca, P.start >= 0, r, o, C, bias, cur, lane, a);
     else if (CAP >= 4 && P.NS == 4) run_program<4, STAGE>(ca, P.start >= 0, r, o, C, bias, cur, lane, a);
     else if (CAP >= 2 && P.NS == 2) run_program<2, STAGE>(ca, P.start >= 0, r, o, C, bias, cur, lane, a);
     else run_program<1, STAGE>(ca, P.start >= 0, r, o, C, bias, cur, lane, a);
+    budget = ca.poll_budget;
   }
 }
 

@@ -223,6 +223,29 @@ def test_spent_budget_is_nan_after_relu_on_the_panel_kernel(N, tile_cols):
             spent(split, ref, tol_fp32(bound, "relu"), budget)
 
 
+@pytest.mark.parametrize("kw,M,tile", [({}, 32, 64), ({"panel_rows": 16, "tile_cols": 256}, 16, 256)])
+def test_budget_is_the_waves_in_total(force, kw, M, tile):
+    """A wave that has spent its budget waits for nothing in its later items either: with one
+    program (panel) and a tile per item, workgroup w takes the tiles w, w + 256, ..., and once
+    one of them is NaN the later ones are."""
+    force(8, 1)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    N = tile * 4 * cus
+    W = inputs.pattern_uniform(M, 512, 0.2, inputs.CFG_TEST, 7720, 0.05)
+    B = torch.ones(512, N, device=DEV)
+    old = os.environ.get("SDNN_POLL_BUDGET")
+    try:
+        with sd.Plan.from_csr(W, **kw) as plan:
+            for budget in (5, 20, 60):
+                os.environ["SDNN_POLL_BUDGET"] = str(budget)
+                nan = np.isnan(run(plan, B, None, "none")[:, ::tile]).reshape(M, 4, cus)
+                assert (nan[:, 1:] >= nan[:, :-1]).all(), f"budget {budget}"
+    finally:
+        os.environ.pop("SDNN_POLL_BUDGET")
+        if old is not None:
+            os.environ["SDNN_POLL_BUDGET"] = old
+
+
 @pytest.mark.parametrize("cap", [2, 4, 8])
 @pytest.mark.parametrize("M,K,N,density", [
     (700, 40, 3092, 0.2), (700, 40, 3001, 0.2),   # rows of C off 64 bytes, past 8 MB

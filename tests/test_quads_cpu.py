@@ -46,3 +46,13 @@ def test_no_wait_on_a_counter_at_its_end():
     lds = [int(n) for n in re.findall(r"lgkmcnt\((\d+)\)", text)]
     loads = [int(n) for n in re.findall(r"vmcnt\((\d+)\)", text)]
     assert lds and max(lds) <= 14 and loads and max(loads) <= 62
+
+
+@pytest.mark.parametrize("header", ["quad_asm_gen.h", "spmm_asm_gen.h"])
+def test_consumer_loops_hand_back_their_poll_budget(header):
+    """A wave runs its loop once per item: the loop returns what is left of the budget, so that the
+    bound on a wave's waiting does not grow with its items."""
+    text = open(os.path.join(ROOT, "paper_2101_07948_amd", "csrc", header)).read()
+    loops = len(re.findall(r"__device__ __forceinline__ void consume_", text))
+    assert loops > 0 and text.count('[budget] "+s"(a.poll_budget)') == loops
+    assert len(re.findall(r"s_mov_b32 %\[budget\], s\d+", text)) == loops
