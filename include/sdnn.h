@@ -138,6 +138,8 @@ typedef struct {
  *   panels:       number of row panels (ceil(M / panel_rows)).
  *   packed_bytes: device bytes of the panel kernel's packed weight streams and their
  *                 indexes.
+ *   quad_packings, quad_kib: packings for the row-quad kernel (a default plan's) and their
+ *                 device memory in KiB, which packed_bytes leaves out.
  *   rho:          nnz / sum over panels of |union of the panel rows' column sets|,
  *                 the reuse an ideal panel kernel gets per staged B row (>= 1).
  *   fill:         nnz / stored stream entries (1.0 = no padding).
@@ -157,9 +159,9 @@ typedef struct {
   int32_t grouping, tile_cols;        /* panel grouping used: 1 consecutive rows of perm,
                                          2 balanced panels (see sdnn_plan_opts.grouping);
                                          the tile_cols option the plan was created with */
-  int32_t tallest_panel_rows, reserved2;  /* fourth packing's height (0: none) */
+  int32_t tallest_panel_rows, quad_packings;  /* fourth packing's height (0: none) */
   double tallest_rho, tallest_fill;
-  int32_t deep_panel_rows, reserved3;     /* fifth packing's height (0: none) */
+  int32_t deep_panel_rows, quad_kib;          /* fifth packing's height (0: none) */
   double deep_rho, deep_fill;
 } sdnn_plan_info_t;
 

@@ -752,9 +752,13 @@ static double fill_of(const Packed& P) {
   return P.stored ? (double)P.nnz / (double)P.stored : 1.0;
 }
 
+static int32_t kib(int64_t bytes) {
+  return (int32_t)std::min<int64_t>((bytes + 1023) / 1024, INT32_MAX);
+}
+
 // Statistics of the first packing, plus the tall and mid ones' if there are.
-static void fill_info(const std::vector<Packed>& packs, int64_t packed_bytes,
-                      const Options& o, sdnn_plan_info_t* out) {
+static void fill_info(const std::vector<Packed>& packs, int64_t packed_bytes, int32_t quad_packings,
+                      int64_t quad_bytes, const Options& o, sdnn_plan_info_t* out) {
   const Packed& P = packs[0];
   out->M = P.M;
   out->K = P.K;
@@ -779,12 +783,12 @@ static void fill_info(const std::vector<Packed>& packs, int64_t packed_bytes,
   out->mid_fill = mid ? fill_of(packs[2]) : 0.0;
   const bool tallest = packs.size() > 3;
   out->tallest_panel_rows = tallest ? packs[3].RW : 0;
-  out->reserved2 = 0;
+  out->quad_packings = quad_packings;
   out->tallest_rho = tallest ? packs[3].rho : 0.0;
   out->tallest_fill = tallest ? fill_of(packs[3]) : 0.0;
   const bool deep = packs.size() > 4;
   out->deep_panel_rows = deep ? packs[4].RW : 0;
-  out->reserved3 = 0;
+  out->quad_kib = kib(quad_bytes);
   out->deep_rho = deep ? packs[4].rho : 0.0;
   out->deep_fill = deep ? fill_of(packs[4]) : 0.0;
   out->grouping = P.grouping;
@@ -812,6 +816,17 @@ static std::vector<int32_t> output_rows(const Packed& P) {
   std::vector<int32_t> out((size_t)std::max(P.M, 1), 0);
   for (int32_t i = 0; i < P.M; ++i) out[P.perm[i]] = P.out_permuted ? i : P.perm[i];
   return out;
+}
+
+// The row-quad packings of a plan; empty where it holds none.
+static std::vector<QuadPacked> pack_all_quads(const CsrView& csr, const Packed& P, const Options& o) {
+  std::vector<QuadPacked> quads;
+  if (!wants_quads(o) || P.M == 0) return quads;
+  const std::vector<int32_t> out_row = output_rows(P);
+  quads.resize(kQuadPackings);
+  for (int i = 0; i < kQuadPackings; ++i)
+    pack_quads(csr.row_ptr, csr.col_idx, csr.values, P.M, P.K, kQuadCaps[i], out_row.data(), &quads[i]);
+  return quads;
 }
 
 static int64_t quad_bytes(const QuadPacked& Q) {
@@ -915,16 +930,15 @@ sdnn_status sdnn_plan_check_host(const int32_t* row_ptr, const int32_t* col_idx,
       bytes += packing_bytes(P, wants_narrow(o));
     }
     if (o.split_chunks > 0) bytes += align256((int64_t)M * 4);  // the device copy of perm
-    if (wants_quads(o)) {
-      const std::vector<int32_t> out_row = output_rows(packs[0]);
-      for (int32_t cap : kQuadCaps) {
-        QuadPacked Q;
-        pack_quads(csr.row_ptr, csr.col_idx, csr.values, M, K, cap, out_row.data(), &Q);
-        if (!check_quads(csr.row_ptr, csr.col_idx, csr.values, M, K, out_row.data(), Q))
-          return SDNN_ERR_INTERNAL;
-      }
+    const std::vector<QuadPacked> quads = pack_all_quads(csr, packs[0], o);
+    const std::vector<int32_t> out_row = output_rows(packs[0]);
+    int64_t qbytes = 0;
+    for (const QuadPacked& Q : quads) {
+      if (!check_quads(csr.row_ptr, csr.col_idx, csr.values, M, K, out_row.data(), Q))
+        return SDNN_ERR_INTERNAL;
+      qbytes += quad_bytes(Q);
     }
-    if (info) fill_info(packs, bytes, o, info);
+    if (info) fill_info(packs, bytes, (int32_t)quads.size(), qbytes, o, info);
     return SDNN_OK;
   } catch (...) {
     return SDNN_ERR_ALLOC;
@@ -974,16 +988,10 @@ sdnn_status sdnn_plan_create(const int32_t* row_ptr, const int32_t* col_idx, con
     if (o.split_chunks > 0) total += align256((int64_t)M * 4);
     plan->packed_bytes = total;
     // the row-quad packings follow (packed_bytes counts the panel packings alone)
-    std::vector<QuadPacked> quads;
+    const std::vector<QuadPacked> quads = pack_all_quads(csr, P0, o);
     const int64_t quad_off = total;
-    if (wants_quads(o) && M > 0) {
-      const std::vector<int32_t> out_row = output_rows(P0);
-      quads.resize(kQuadPackings);
-      for (int i = 0; i < kQuadPackings; ++i) {
-        pack_quads(csr.row_ptr, csr.col_idx, csr.values, M, K, kQuadCaps[i], out_row.data(), &quads[i]);
-        total += quad_bytes(quads[i]);
-      }
-    }
+    for (const QuadPacked& Q : quads) total += quad_bytes(Q);
+    plan->quad_bytes = total - quad_off;
     if (total > 0) {
       if (hipMalloc(&plan->d_mem, (size_t)total) != hipSuccess) {
         (void)hipGetLastError();
@@ -1120,12 +1128,12 @@ sdnn_status sdnn_plan_info(sdnn_plan p, sdnn_plan_info_t* out) {
   out->tile_cols = p->tile_cols;
   const bool tallest = p->npack > 3;
   out->tallest_panel_rows = tallest ? p->pk[3].RW : 0;
-  out->reserved2 = 0;
+  out->quad_packings = p->nquads;
   out->tallest_rho = tallest ? p->pk[3].rho : 0.0;
   out->tallest_fill = tallest ? p->pk[3].fill : 0.0;
   const bool deep = p->npack > 4;
   out->deep_panel_rows = deep ? p->pk[4].RW : 0;
-  out->reserved3 = 0;
+  out->quad_kib = kib(p->quad_bytes);
   out->deep_rho = deep ? p->pk[4].rho : 0.0;
   out->deep_fill = deep ? p->pk[4].fill : 0.0;
   return SDNN_OK;

@@ -264,6 +264,7 @@ struct sdnn_plan_s {
   sdnn::DevPacking pk[sdnn::kMaxPackings];
   int nquads = 0;              // quad packings (default plans: panel_rows = 0, tile_cols = 0)
   sdnn::DevQuads quads[sdnn::kQuadPackings];
+  int64_t quad_bytes = 0;      // of their device memory
   sdnn::TunedShape tuned[sdnn::kTunedSlots];  // filled by sdnn_plan_tune
   int32_t ntuned = 0;
 };
