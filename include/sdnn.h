@@ -60,12 +60,12 @@ typedef enum {
 /* Options for sdnn_plan_create; pass NULL for the defaults {0, 1, 0, 0, NULL, 0, 0}.
  *   panel_rows:   rows per register panel of the panel kernel.  0 (default) packs W four
  *                 times, with panels of 4, 12, 8 and 16 rows, and a fifth time with 32-row
- *                 panels for 128-column tiles unless tile_cols = 256; with tile_cols = 0
- *                 too (a default plan), also for the row-quad kernel, which then serves
- *                 sdnn_spmm and sdnn_conv3x3 (same result bit for bit; products unless
- *                 sdnn_plan_tune measured the panel kernel faster at N).  The panel
- *                 kernel, which serves the K-split calls and plans that fix panel_rows or
- *                 tile_cols, picks one packing per call: the 32-row panels (with 12
+ *                 panels for 128-column tiles unless tile_cols = 256; with tile_cols
+ *                 and grouping 0 too (a default plan), also for the row-quad kernel, which
+ *                 then serves sdnn_spmm and sdnn_conv3x3 (same result bit for bit; products
+ *                 unless sdnn_plan_tune measured the panel kernel faster at N).  The panel
+ *                 kernel, which serves the K-split calls and plans that fix panel_rows,
+ *                 grouping or tile_cols, picks one packing per call: the 32-row panels (with 12
  *                 consumer waves per workgroup) when W holds under 20 entries per 16 rows
  *                 and 32 columns and their grid fills the compute units; otherwise the
  *                 fewest rounds of workgroups over the compute units, then the most units
@@ -111,7 +111,8 @@ typedef enum {
  *                 choice, at present balanced panels: the panels of a workgroup advance
  *                 together through the staged chunks of B, so the heaviest panel, and
  *                 the one whose nonzeros bunch into the fewest chunks, set the pace.
- *                 Outside 0..2: SDNN_ERR_DIM.
+ *                 1 and 2 also keep the plan's calls on the panel kernel (the row-quad
+ *                 kernel groups rows by their length).  Outside 0..2: SDNN_ERR_DIM.
  *   tile_cols:    columns of C per workgroup tile (the microkernel's output tile width,
  *                 Sec. 3.2.2).  0 (default) = the plan holds its stream for tiles of 256
  *                 columns (4 per lane, one workgroup per compute unit) and for tiles of 128

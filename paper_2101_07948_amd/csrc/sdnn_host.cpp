@@ -808,8 +808,11 @@ static int64_t packing_bytes(const Packed& P, bool narrow) {
 // Plans serve 128-column tiles unless the option fixes 256.
 static bool wants_narrow(const Options& o) { return o.tile_cols != kTileCols; }
 
-// Default plans (no panel height or tile width fixed) also hold the row-quad packings.
-static bool wants_quads(const Options& o) { return o.rws.size() > 1 && o.tile_cols == 0; }
+// Default plans (no panel height, grouping or tile width fixed: options of the panel kernel, which
+// the row-quad kernel would leave without effect) also hold the row-quad packings.
+static bool wants_quads(const Options& o) {
+  return o.rws.size() > 1 && o.tile_cols == 0 && o.grouping == 0;
+}
 
 // The row of C each source row is stored to.
 static std::vector<int32_t> output_rows(const Packed& P) {

@@ -27,12 +27,14 @@ def test_random_patterns(M, K, density):
 
 def test_info_reports_the_packings_and_their_memory():
     """quad_packings and quad_kib: at least 8 bytes per entry and packing for a default plan, none
-    for a plan that fixes a panel height or a tile width."""
+    for a plan that fixes a panel height, a grouping or a tile width: these are the
+    panel kernel's, and its calls stay there."""
     rp, ci, v, _ = random_csr(np.random.default_rng(3), 256, 512, 0.1)
     info = sd.plan_check_host(rp, ci, v, 256, 512)
     assert info["quad_packings"] == 4
     assert 4 * 8 * len(ci) <= 1024 * info["quad_kib"] <= 4 * 16 * len(ci)
-    for kw in ({"panel_rows": 8}, {"tile_cols": 128}, {"tile_cols": 256}):
+    for kw in ({"panel_rows": 8}, {"tile_cols": 128}, {"tile_cols": 256}, {"grouping": "order"},
+               {"grouping": "balanced"}):
         info = sd.plan_check_host(rp, ci, v, 256, 512, **kw)
         assert info["quad_packings"] == 0 and info["quad_kib"] == 0
 
