@@ -139,8 +139,9 @@ typedef struct {
  *   panels:       number of row panels (ceil(M / panel_rows)).
  *   packed_bytes: device bytes of the panel kernel's packed weight streams and their
  *                 indexes.
- *   quad_packings, quad_kib: packings for the row-quad kernel (a default plan's) and their
- *                 device memory in KiB, which packed_bytes leaves out.
+ *   quad_packings, quad_kib: packings for the row-quad kernel (a default plan's: up to four;
+ *                 one that would take more than half of packed_bytes, and 1 MiB, is left
+ *                 out) and their device memory in KiB, which packed_bytes leaves out.
  *   rho:          nnz / sum over panels of |union of the panel rows' column sets|,
  *                 the reuse an ideal panel kernel gets per staged B row (>= 1).
  *   fill:         nnz / stored stream entries (1.0 = no padding).

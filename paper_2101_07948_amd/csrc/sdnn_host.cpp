@@ -821,14 +821,18 @@ static std::vector<int32_t> output_rows(const Packed& P) {
   return out;
 }
 
-// The row-quad packings of a plan; empty where it holds none.
-static std::vector<QuadPacked> pack_all_quads(const CsrView& csr, const Packed& P, const Options& o) {
+// The row-quad packings of a plan whose panel packings take panel_bytes; empty where it holds none.
+static std::vector<QuadPacked> pack_all_quads(const CsrView& csr, const Packed& P, const Options& o,
+                                              int64_t panel_bytes) {
   std::vector<QuadPacked> quads;
   if (!wants_quads(o) || P.M == 0) return quads;
   const std::vector<int32_t> out_row = output_rows(P);
-  quads.resize(kQuadPackings);
-  for (int i = 0; i < kQuadPackings; ++i)
-    pack_quads(csr.row_ptr, csr.col_idx, csr.values, P.M, P.K, kQuadCaps[i], out_row.data(), &quads[i]);
+  for (int32_t cap : kQuadCaps) {
+    quads.emplace_back();
+    if (!pack_quads(csr.row_ptr, csr.col_idx, csr.values, P.M, P.K, cap, out_row.data(),
+                    quad_max_bytes(panel_bytes), &quads.back()))
+      quads.pop_back();
+  }
   return quads;
 }
 
@@ -933,7 +937,7 @@ sdnn_status sdnn_plan_check_host(const int32_t* row_ptr, const int32_t* col_idx,
       bytes += packing_bytes(P, wants_narrow(o));
     }
     if (o.split_chunks > 0) bytes += align256((int64_t)M * 4);  // the device copy of perm
-    const std::vector<QuadPacked> quads = pack_all_quads(csr, packs[0], o);
+    const std::vector<QuadPacked> quads = pack_all_quads(csr, packs[0], o, bytes);
     const std::vector<int32_t> out_row = output_rows(packs[0]);
     int64_t qbytes = 0;
     for (const QuadPacked& Q : quads) {
@@ -991,7 +995,7 @@ sdnn_status sdnn_plan_create(const int32_t* row_ptr, const int32_t* col_idx, con
     if (o.split_chunks > 0) total += align256((int64_t)M * 4);
     plan->packed_bytes = total;
     // the row-quad packings follow (packed_bytes counts the panel packings alone)
-    const std::vector<QuadPacked> quads = pack_all_quads(csr, P0, o);
+    const std::vector<QuadPacked> quads = pack_all_quads(csr, P0, o, plan->packed_bytes);
     const int64_t quad_off = total;
     for (const QuadPacked& Q : quads) total += quad_bytes(Q);
     plan->quad_bytes = total - quad_off;

@@ -170,9 +170,21 @@ struct QuadPacked {
 };
 constexpr double kQuadSlack = 1.4;
 
-// Packs W (validated CSR); out_row[i] is the row of C that row i is stored to.
-void pack_quads(const int32_t* row_ptr, const int32_t* col_idx, const float* values, int32_t M,
-                int32_t K, int32_t cap, const int32_t* out_row, QuadPacked* out);
+// Packs W (validated CSR); out_row[i] is the row of C that row i is stored to.  False, with *out
+// left empty, once the stream takes more than max_bytes.
+bool pack_quads(const int32_t* row_ptr, const int32_t* col_idx, const float* values, int32_t M,
+                int32_t K, int32_t cap, const int32_t* out_row, int64_t max_bytes, QuadPacked* out);
+// The bytes a packing may take in a plan whose panel packings take panel_bytes; one that needs
+// more is left out of the plan.  A block is 256 bytes however few entries it holds, so rows whose
+// entries lie far apart in K, from one another or from the other rows', fill the stream with
+// filler: 4096 rows of 16 neighbouring entries each, scattered over K = 8000, take 28, 49, 77 and
+// 108 bytes an entry in the four packings (768 x 3072 at 90 %: 8.5) against 83 of the panel
+// packings, and the last three are left out.
+// Uniform rows of few entries keep all (4096 x 524288 at 99.99 %: 125 to 225 bytes an entry
+// against 556 of the panel packings; N = 64: 1.44 ms, on the panel kernel 3.43).
+inline int64_t quad_max_bytes(int64_t panel_bytes) {
+  return panel_bytes / 2 > (1 << 20) ? panel_bytes / 2 : 1 << 20;
+}
 // Walks the packed form and checks that every entry appears once, in its row, in ascending
 // column order, with unchanged bits, within the window its descriptor states.
 bool check_quads(const int32_t* row_ptr, const int32_t* col_idx, const float* values, int32_t M,

@@ -18,8 +18,8 @@ static int quad_window(const int32_t* row_ptr, int32_t M, int32_t K) {
   return d >= 0.2 ? kQuadMaxWindow - 3 : d >= 0.08 ? kQuadMaxWindow - 2 : kQuadMaxWindow;
 }
 
-void pack_quads(const int32_t* row_ptr, const int32_t* col_idx, const float* values, int32_t M,
-                int32_t K, int32_t cap, const int32_t* out_row, QuadPacked* out) {
+bool pack_quads(const int32_t* row_ptr, const int32_t* col_idx, const float* values, int32_t M,
+                int32_t K, int32_t cap, const int32_t* out_row, int64_t max_bytes, QuadPacked* out) {
   QuadPacked& Q = *out;
   Q = QuadPacked();
   Q.cap = cap;
@@ -71,6 +71,10 @@ void pack_quads(const int32_t* row_ptr, const int32_t* col_idx, const float* val
         const int64_t limit = ((int64_t)clo + window) * kQuadChunk;  // first column not taken
         int32_t high = low;
         const size_t base = Q.stream.size();
+        if ((int64_t)base * 4 >= max_bytes) {
+          Q = QuadPacked();
+          return false;
+        }
         Q.stream.resize(base + 64);
         uint32_t* blk = Q.stream.data() + base;
         for (int j = 0; j < RW; ++j) {
@@ -129,6 +133,7 @@ void pack_quads(const int32_t* row_ptr, const int32_t* col_idx, const float* val
       Q.outs[(size_t)p * cap * 4 + j] = out_row[row];
     }
   }
+  return true;
 }
 
 bool check_quads(const int32_t* row_ptr, const int32_t* col_idx, const float* values, int32_t M,

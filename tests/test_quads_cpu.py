@@ -39,6 +39,30 @@ def test_info_reports_the_packings_and_their_memory():
         assert info["quad_packings"] == 0 and info["quad_kib"] == 0
 
 
+def scattered_runs(M, K, n, seed):
+    """M rows of n neighbouring entries each, at random places."""
+    start = np.random.default_rng(seed).integers(0, K - n + 1, M)
+    cols = (start[:, None] + np.arange(n)).astype(np.int32).ravel()
+    return np.arange(0, M * n + 1, n, dtype=np.int32), cols, np.ones(M * n, np.float32)
+
+
+@pytest.mark.parametrize("M,K,rows", [(4096, 8000, "runs"), (4096, 60000, "runs"),
+                                      (2048, 262144, "uniform"), (20000, 50000, "uniform")])
+def test_memory_stays_within_the_panel_packings(M, K, rows):
+    """Rows whose entries a block cannot put together (16 neighbours scattered over K; 26 or 2
+    entries spread over all of K): the row-quad packings together take at most twice what the panel
+    packings take, a packing that would take more than its share is left out."""
+    if rows == "runs":
+        rp, ci, v = scattered_runs(M, K, 16, M + K)
+    else:
+        n = 26 if K > 100000 else 2
+        ci = np.sort(np.random.default_rng(M).integers(0, K // n, (M, n)) + np.arange(n) * (K // n), 1)
+        rp, ci, v = np.arange(0, M * n + 1, n, dtype=np.int32), ci.astype(np.int32).ravel(), np.ones(M * n, np.float32)
+    info = sd.plan_check_host(rp, ci, v, M, K, permute="identity")
+    assert 1024 * info["quad_kib"] <= 2 * info["packed_bytes"]
+    assert (info["quad_packings"] < 4) == (rows == "runs")
+
+
 def test_empty_and_extreme_rows():
     """No entries at all, one full row among empty ones, and rows at opposite ends of K (fillers
     everywhere, more than 64 descriptors in a program)."""
