@@ -217,13 +217,29 @@ def _blas_time(Wd, B, C, reps=20):
 
 
 def _packing_used(plan, N):
-    """(panel height, rho) of the packing plan.spmm runs on at N, as the library reports."""
+    """(panel height, rho) of the panel kernel's packing at N, as the library reports."""
     rw = plan.launch_shape(N)["panel_rows"]
     info = plan.info
     for k in ("", "tall_", "mid_", "tallest_", "deep_"):
         if info[k + "panel_rows"] == rw:
             return rw, info[k + "rho"]
     return rw, float("nan")
+
+
+def _launch_used(plan, N):
+    """The launch of plan.spmm at N, as the library reports it: kernel, rows (of the largest
+    programs, or of a panel), consumer waves per workgroup, tile columns, and rho of the packing
+    (the row-quad kernel's programs have none)."""
+    q = plan.launch_quads(N)
+    if q:
+        return {"kernel": "row quads", "rows": q["program_rows"], "waves": q["waves"], "tile_cols": 64, "rho": None}
+    sh = plan.launch_shape(N)
+    return {"kernel": "panels", "rows": sh["panel_rows"], "waves": sh["waves"], "tile_cols": sh["tile_cols"],
+            "rho": round(_packing_used(plan, N)[1], 4)}
+
+
+def _launch_text(u):
+    return f"{u['kernel']}: {u['rows']} x {u['waves']}, {u['tile_cols']}"
 
 
 def run_suite(out_path):
@@ -248,10 +264,11 @@ def run_suite(out_path):
              f"{ALU_PEAK_TFLOPS:.1f} TFLOP/s (FP32 vector peak), % HBM of {HBM_PEAK_GBS:.0f} GB/s "
              "(algorithmic bytes 8 nnz + 4 KN + 4 MN + 4 M).", "",
              "## Every configuration", "",
-             "Launch: panel rows x consumer waves per workgroup, tile columns, as the default "
-             "plan picks them.  '256-col us': a plan fixed to 256-column tiles (tile_cols = "
+             "Launch: kernel, rows of its largest programs or of its panels x consumer waves per "
+             "workgroup, tile columns, as the default plan picks them; rho of the panels.  "
+             "'256-col us': a plan fixed to 256-column tiles of the panel kernel (tile_cols = "
              "256, four packings), cold mean.  'tuned': after sdnn_plan_tune at this N, cold "
-             "mean and the shape it recorded.", "",
+             "mean and the launch it recorded.", "",
              "| layer | nnz | launch | rho | cold median us (p10-p90) | cold mean us | "
              "warm median us | GFLOP/s (cold mean) | % ALU | alg GB/s | % HBM | 256-col us | "
              "tuned us (shape) |",
@@ -260,11 +277,11 @@ def run_suite(out_path):
     for label, L, N in _suite_layers():
         W = L.W
         with sd.Plan.from_csr(W) as plan:
-            rw, rho = _packing_used(plan, N)
-            sh = plan.launch_shape(N)
+            use = _launch_used(plan, N)
             per, mean, nsets = _time_layer(plan, L, N)
             wper, _, _ = _time_layer(plan, L, N, cold=False)
-            tsh = plan.tune(N, torch.randn(W.K, N, device=dev), torch.empty(W.M, N, device=dev))
+            plan.tune(N, torch.randn(W.K, N, device=dev), torch.empty(W.M, N, device=dev))
+            tuned = _launch_used(plan, N)
             _, tmean, _ = _time_layer(plan, L, N)
         with sd.Plan.from_csr(W, tile_cols=256) as plan:
             _, mean256, _ = _time_layer(plan, L, N)
@@ -272,13 +289,14 @@ def run_suite(out_path):
         ab = 8.0 * W.nnz + 4.0 * W.K * N + 4.0 * W.M * N + 4.0 * W.M
         t = mean * 1e-3
         timed[label] = mean
-        lines.append(f"| {label} | {W.nnz} | {rw} x {sh['waves']}, {sh['tile_cols']} | {rho:.2f} | "
+        lines.append(f"| {label} | {W.nnz} | {_launch_text(use)} | "
+                     f"{'-' if use['rho'] is None else round(use['rho'], 2)} | "
                      f"{_pct(per, .5)*1e3:.1f} "
                      f"({_pct(per, .1)*1e3:.1f}-{_pct(per, .9)*1e3:.1f}) | {mean*1e3:.1f} | "
                      f"{_pct(wper, .5)*1e3:.1f} | {flop/t/1e9:.0f} | "
                      f"{100*flop/t/1e12/ALU_PEAK_TFLOPS:.1f} | {ab/t/1e9:.0f} | "
                      f"{100*ab/t/1e9/HBM_PEAK_GBS:.1f} | {mean256*1e3:.1f} | {tmean*1e3:.1f} "
-                     f"({tsh['panel_rows']} x {tsh['waves']}, {tsh['tile_cols']}) |")
+                     f"({_launch_text(tuned)}) |")
         print(lines[-1], flush=True)
 
     lines += ["", "## Dense comparison: the library's FP32 GEMM kernel (same layouts and epilogue) "
@@ -500,9 +518,8 @@ def run_suite(out_path):
             return _launch_times(fn, 50)[1]
         with sd.Plan.from_csr(W) as plan:
             base = timed_mean(plan, None)
-            rw, _ = _packing_used(plan, N)
-            tile = plan.launch_shape(N)["tile_cols"] if ch is None else 256
-        grid = f"{-(-N // tile)} x {-(-W.M // rw)} ({rw}-row, {tile}-col)"
+            use = _launch_used(plan, N) if ch is None else None  # (a product's; none for a convolution's)
+        grid = f"{-(-N // use['tile_cols'])} x {-(-W.M // use['rows'])} ({_launch_text(use)})" if use else "row quads"
         with sd.Plan.from_csr(W, split_chunks=S) as plan:
             ws = torch.empty(max(plan.workspace_floats(N), 1), device=dev)
             auto = timed_mean(plan, ws, 0)
@@ -690,7 +707,6 @@ def main():
         w.B = inputs.dense_B(L.W.K, w.N, inputs.CFG_TEST, 4242)
     W, N, M, K = L.W, w.N, L.W.M, L.W.K
     plan = sd.Plan.from_csr(W, grouping=args.grouping)
-    info = plan.info
 
     bytes_set = 4 * (K * N + M * N)
     nsets = 1 if args.warm else max(1, math.ceil((1 << 30) / bytes_set))
@@ -805,8 +821,8 @@ def main():
         "config": {"workload": ("w0: W 768x3072 fp32, 90% uniform-random sparsity, "
                                 f"B 3072x{N} fp32, bias, no activation") if args.layer == "w0"
                    else f"{args.layer}: W {M}x{K} fp32 (nnz {W.nnz}), B {K}x{N} fp32, bias, {L.epi}",
-                   "M": M, "K": K, "N": N, "nnz": W.nnz, "panel_rows": info["panel_rows"],
-                   "rho": round(info["rho"], 4), "buffer_sets": nsets},
+                   "M": M, "K": K, "N": N, "nnz": W.nnz, "launch": _launch_used(plan, N),
+                   "buffer_sets": nsets},
         "alg_GBps": round(gbs, 1),
         "roofline": roof,
         "cpu_baseline": cpu,

@@ -285,6 +285,15 @@ sdnn_status sdnn_spmm_split_noalloc(sdnn_plan p, const float* B, float* C, int32
  * Errors: SDNN_ERR_NULL (p), SDNN_ERR_DIM (N <= 0 or M = 0). */
 sdnn_status sdnn_plan_launch_shape(sdnn_plan p, int32_t N, int32_t* panel_rows, int32_t* waves);
 
+/* The row-quad launch sdnn_spmm uses for this plan at N columns when B and C are 64-byte
+ * aligned: *program_rows = rows of the packing's largest programs (4, 8, 16 or 32),
+ * *waves = consumer waves per workgroup, on tiles of 64 columns (either pointer may be
+ * NULL).  Both 0 where sdnn_spmm runs on the panel kernel, whose shape
+ * sdnn_plan_launch_shape and sdnn_plan_launch_tile give.  Host only.
+ * Errors: SDNN_ERR_NULL (p), SDNN_ERR_DIM (N <= 0 or M = 0). */
+sdnn_status sdnn_plan_launch_quads(sdnn_plan p, int32_t N, int32_t* program_rows,
+                                   int32_t* waves);
+
 /* The workgroups along K that sdnn_spmm_split runs for this plan at N columns when asked
  * for `splits` (0: the library's choice, see sdnn_spmm_split); 1 for a plan without
  * K-segments.  Host only.  Errors: SDNN_ERR_NULL (p or runs), SDNN_ERR_DIM (N <= 0, M = 0,

@@ -88,6 +88,7 @@ def lib() -> ctypes.CDLL:
         L.sdnn_plan_tune.argtypes = [p, p, p, i32, p, p, p]
         L.sdnn_plan_launch_shape.argtypes = [p, i32, p, p]
         L.sdnn_plan_launch_tile.argtypes = [p, i32, p]
+        L.sdnn_plan_launch_quads.argtypes = [p, i32, p, p]
         L.sdnn_plan_split_runs.argtypes = [p, i32, i32, p]
         i64 = ctypes.c_int64
         L.sdnn_spmm_split.argtypes = [p, p, p, i32, p, ctypes.c_int, i32, p, i64, p]
@@ -97,7 +98,7 @@ def lib() -> ctypes.CDLL:
                    "sdnn_plan_get_perm", "sdnn_plan_info", "sdnn_spmm", "sdnn_dense_gemm",
                    "sdnn_conv3x3", "sdnn_plan_tune", "sdnn_spmm_split", "sdnn_conv3x3_split",
                    "sdnn_plan_launch_shape", "sdnn_spmm_split_noalloc", "sdnn_plan_launch_tile",
-                   "sdnn_plan_split_runs"):
+                   "sdnn_plan_launch_quads", "sdnn_plan_split_runs"):
             getattr(L, fn).restype = ctypes.c_int
         _lib_handle = L
     return _lib_handle
@@ -279,14 +280,24 @@ class Plan:
         return info.as_dict()
 
     def launch_shape(self, N: int) -> dict:
-        """The panel height, consumer waves per workgroup and tile width spmm uses at N
-        columns (the tile width for 16-byte aligned B and C with N % 4 == 0)."""
+        """The panel kernel's panel height, consumer waves per workgroup and tile width at N
+        columns (the tile width for 16-byte aligned B and C with N % 4 == 0); spmm runs on
+        that kernel where launch_quads is None."""
         rw, waves, tile = ctypes.c_int32(), ctypes.c_int32(), ctypes.c_int32()
         _check(self._lib.sdnn_plan_launch_shape(self.handle, int(N), ctypes.byref(rw),
                                                 ctypes.byref(waves)), "sdnn_plan_launch_shape")
         _check(self._lib.sdnn_plan_launch_tile(self.handle, int(N), ctypes.byref(tile)),
                "sdnn_plan_launch_tile")
         return {"panel_rows": rw.value, "waves": waves.value, "tile_cols": tile.value}
+
+    def launch_quads(self, N: int):
+        """The row-quad launch spmm uses at N columns (for 64-byte aligned B and C): rows of
+        the packing's largest programs and consumer waves per workgroup; None where spmm runs
+        on the panel kernel (launch_shape)."""
+        rows, waves = ctypes.c_int32(), ctypes.c_int32()
+        _check(self._lib.sdnn_plan_launch_quads(self.handle, int(N), ctypes.byref(rows),
+                                                ctypes.byref(waves)), "sdnn_plan_launch_quads")
+        return {"program_rows": rows.value, "waves": waves.value} if rows.value else None
 
     def tune(self, N: int, B=None, C=None, stream=None) -> dict:
         """Times the plan's launch shapes at this N (on B / C, allocated here when not

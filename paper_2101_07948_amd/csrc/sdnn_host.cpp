@@ -1253,6 +1253,16 @@ sdnn_status sdnn_plan_launch_shape(sdnn_plan p, int32_t N, int32_t* panel_rows, 
   return SDNN_OK;
 }
 
+sdnn_status sdnn_plan_launch_quads(sdnn_plan p, int32_t N, int32_t* program_rows, int32_t* waves) {
+  if (!p) return SDNN_ERR_NULL;
+  if (N <= 0 || p->M == 0) return SDNN_ERR_DIM;
+  int32_t rows = 0, w = 0;
+  launch_quad_shape(p, N, &rows, &w);
+  if (program_rows) *program_rows = rows;
+  if (waves) *waves = w;
+  return SDNN_OK;
+}
+
 sdnn_status sdnn_plan_split_runs(sdnn_plan p, int32_t N, int32_t splits, int32_t* runs) {
   if (!p || !runs) return SDNN_ERR_NULL;
   if (N <= 0 || p->M == 0 || splits < 0) return SDNN_ERR_DIM;

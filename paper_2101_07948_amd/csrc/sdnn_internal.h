@@ -313,9 +313,13 @@ void launch_shape(const sdnn_plan_s* p, int32_t N, int32_t* panel_rows, int32_t*
 // and records the fastest in p->tuned.
 hipError_t tune_spmm(sdnn_plan_s* p, const float* B, float* C, int32_t N, hipStream_t stream,
                      TunedShape* chosen);
+// The row-quad launch of a product at N columns (rows of the packing's largest programs and
+// consumer waves; 0 and 0 where the product runs on the panel kernel).
+void launch_quad_shape(const sdnn_plan_s* p, int32_t N, int32_t* program_rows, int32_t* waves);
 // The row-quad kernel (sdnn_quad.hip): whether it serves the plan's calls at N columns, the
-// launch it picks at N, and its launch (conv_hwn: H, W and the images of a 3x3 convolution
-// whose input is B, or null).
+// launch it picks at N, the consumer waves a launch has, and its launch (conv_hwn: H, W and the
+// images of a 3x3 convolution whose input is B, or null).
+int quad_waves(const sdnn_plan_s* p, const QuadCfg& cfg);
 bool quads_serve(const sdnn_plan_s* p, int32_t N);
 QuadCfg quad_shape(const sdnn_plan_s* p, const float* B, const float* C, int32_t N, bool conv);
 hipError_t launch_quads(const sdnn_plan_s* p, const float* B, float* C, int32_t N,

@@ -884,16 +884,29 @@ void launch_shape(const sdnn_plan_s* p, int32_t N, int32_t* panel_rows, int32_t*
   *tile_cols = tw;
 }
 
+// Whether a product runs on the row-quad kernel, and its launch there.
+static bool product_on_quads(const sdnn_plan_s* p, const float* B, const float* C, int32_t N, QuadCfg* cfg) {
+  if (!quads_serve(p, N)) return false;
+  for (int i = 0; i < p->ntuned; ++i)
+    if (p->tuned[i].N == N) {
+      *cfg = p->tuned[i].quad;
+      return p->tuned[i].quads != 0;
+    }
+  *cfg = quad_shape(p, B, C, N, false);
+  return true;
+}
+
+void launch_quad_shape(const sdnn_plan_s* p, int32_t N, int32_t* program_rows, int32_t* waves) {
+  QuadCfg cfg;
+  const bool quads = product_on_quads(p, nullptr, nullptr, N, &cfg);
+  *program_rows = quads ? 4 * p->quads[cfg.pack].cap : 0;
+  *waves = quads ? quad_waves(p, cfg) : 0;
+}
+
 hipError_t launch_spmm(const sdnn_plan_s* p, const float* B, float* C, int32_t N,
                        const float* bias, int epi, hipStream_t stream) {
-  if (quads_serve(p, N)) {
-    const TunedShape* t = nullptr;
-    for (int i = 0; i < p->ntuned; ++i)
-      if (p->tuned[i].N == N) t = &p->tuned[i];
-    if (!t || t->quads)
-      return launch_quads(p, B, C, N, bias, epi, nullptr, t ? t->quad : quad_shape(p, B, C, N, false),
-                          stream);
-  }
+  QuadCfg cfg;
+  if (product_on_quads(p, B, C, N, &cfg)) return launch_quads(p, B, C, N, bias, epi, nullptr, cfg, stream);
   return launch_panels(p, B, C, N, bias, epi, nullptr, nullptr, nullptr, 0, stream);
 }
 

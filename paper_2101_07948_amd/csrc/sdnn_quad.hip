@@ -594,12 +594,16 @@ QuadCfg quad_shape(const sdnn_plan_s* p, const float* B, const float* C, int32_t
   return c;
 }
 
+int quad_waves(const sdnn_plan_s* p, const QuadCfg& cfg) {
+  return std::max(1, std::min({cfg.waves, kMaxQuadConsumers, p->quads[cfg.pack].nprogs}));
+}
+
 hipError_t launch_quads(const sdnn_plan_s* p, const float* B, float* C, int32_t N,
                         const float* bias, int epi, const int32_t* conv_hwn, const QuadCfg& cfg,
                         hipStream_t stream) {
   const DevQuads& d = p->quads[cfg.pack];
   const int64_t cus = p->num_cus > 0 ? p->num_cus : 256;
-  const int waves = std::max(1, std::min({cfg.waves, kMaxQuadConsumers, d.nprogs}));
+  const int waves = quad_waves(p, cfg);
   QuadArgs args;
   args.K = p->K;
   args.N = N;

@@ -256,6 +256,7 @@ def test_bad_dims_and_nulls():
     assert L.sdnn_plan_get_perm(None, P(perm)) == 1
     assert L.sdnn_plan_info(None, ctypes.byref(info)) == 1
     assert L.sdnn_spmm(None, None, None, 4, None, 0, None) == 1
+    assert L.sdnn_plan_launch_quads(None, 4, None, None) == 1
     assert L.sdnn_dense_gemm(None, None, None, -1, 4, 4, None, 0, None) == 2
     assert L.sdnn_dense_gemm(None, None, None, 0, 4, 4, None, 0, None) == 0  # M = 0: no-op
 

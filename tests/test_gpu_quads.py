@@ -258,3 +258,40 @@ def test_output_stores(force, cap, M, K, N, density):
     force(cap, 12)
     W = inputs.pattern_uniform(M, K, density, inputs.CFG_TEST, 7300 + M + K, 0.05)
     check(W, N, f"stores cap {cap} M {M} K {K}")
+
+
+def test_reported_launch(force):
+    """sdnn_plan_launch_quads reports the launch of products: programs and waves of a default plan
+    (forced ones, clipped to the programs there are), none for a plan that fixes an option of the
+    panel kernel or for rows of B too long for the staging; and the info's packings."""
+    W = inputs.pattern_grouped8(96, 200, 0.16, inputs.CFG_TEST, 7800, 0.05)
+    with sd.Plan.from_csr(W) as plan:
+        got = plan.launch_quads(64)
+        assert got["program_rows"] in (4, 8, 16, 32) and 1 <= got["waves"] <= 12
+        assert plan.launch_quads(1 << 25) is None
+        assert plan.info["quad_packings"] == 4 and plan.info["quad_kib"] > 0
+        host = sd.plan_check_host(W.row_ptr, W.col_idx, W.values, W.M, W.K)
+        assert all(host[k] == plan.info[k] for k in ("quad_packings", "quad_kib", "packed_bytes"))
+        for cap, waves, want in ((1, 12, 12), (4, 5, 5), (8, 12, 3)):
+            force(cap, waves)
+            assert plan.launch_quads(64) == {"program_rows": 4 * cap, "waves": want}
+        for bad in (0, -1):
+            with pytest.raises(sd.SdnnError) as ei:
+                plan.launch_quads(bad)
+            assert ei.value.code == 2
+    for kw in ({"panel_rows": 8}, {"grouping": "order"}, {"grouping": "balanced"}, {"tile_cols": 128}):
+        with sd.Plan.from_csr(W, **kw) as plan:
+            assert plan.launch_quads(64) is None
+
+
+def test_tuned_launch_is_the_one_calls_run_on():
+    """After sdnn_plan_tune the reported launch is one that was timed, and calls agree with the panel
+    kernel bit for bit."""
+    W = inputs.pattern_uniform(512, 512, 0.2, inputs.CFG_TEST, 7810, 0.05)
+    B = torch.from_numpy(inputs.dense_B(512, 784, inputs.CFG_TEST, 7811)).to(DEV)
+    with sd.Plan.from_csr(W) as plan, sd.Plan.from_csr(W, panel_rows=4) as panel:
+        rule = plan.launch_quads(784)
+        plan.tune(784, B, torch.empty(512, 784, device=DEV))
+        got = plan.launch_quads(784)
+        assert got is None or got == rule or got["waves"] in (3, 6, 9, 12)
+        assert np.array_equal(run(plan, B, None, "none"), run(panel, B, None, "none"))
