@@ -44,7 +44,7 @@ ALU_PEAK_TFLOPS = 256 * 128 * 2 * 2.4e9 / 1e12
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2101_07948_amd", "csrc", f)
                   for f in ("sdnn_kernels.hip", "sdnn_host.cpp", "sdnn_internal.h",
                             "gen_spmm_asm.py", "spmm_asm_gen.h", "sdnn_quad.hip", "sdnn_quad_pack.cpp",
-                            "sdnn_device.h", "gen_quad_asm.py")]
+                            "sdnn_device.h", "gen_quad_asm.py", "quad_asm_gen.h")]
 def traffic_file(layer: str = "w0") -> str:
     return os.path.join(ROOT, "profiles", f"traffic_spmm_{layer}.json")
 

@@ -261,14 +261,20 @@ def test_bad_dims_and_nulls():
     assert L.sdnn_dense_gemm(None, None, None, 0, 4, 4, None, 0, None) == 0  # M = 0: no-op
 
 
-def test_generated_kernel_header_in_sync():
-    """The K-loop assembly header is generated; the committed copy must match."""
+@pytest.mark.parametrize("name,header", [("gen_spmm_asm", "spmm_asm_gen.h"), ("gen_quad_asm", "quad_asm_gen.h")])
+def test_generated_kernel_header_in_sync(name, header):
+    """The loops' assembly headers are generated; the committed copies must match, and
+    bench.py's kernel hash covers both them and their generators."""
     import importlib.util
-    path = os.path.join(ROOT, "paper_2101_07948_amd", "csrc", "gen_spmm_asm.py")
-    spec = importlib.util.spec_from_file_location("gen_spmm_asm", path)
-    gen = importlib.util.module_from_spec(spec)
-    spec.loader.exec_module(gen)
-    assert gen.main(check=True) == 0, "spmm_asm_gen.h is stale: run the package build"
+    def load(path, as_name):
+        spec = importlib.util.spec_from_file_location(as_name, path)
+        mod = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(mod)
+        return mod
+    gen = load(os.path.join(ROOT, "paper_2101_07948_amd", "csrc", name + ".py"), name)
+    assert gen.main(check=True) == 0, f"{header} is stale: run the package build"
+    hashed = {os.path.basename(f) for f in load(os.path.join(ROOT, "bench.py"), "bench_under_test").KERNEL_SOURCES}
+    assert {name + ".py", header} <= hashed
 
 
 @pytest.mark.parametrize("grouping", ["order", "balanced"])
