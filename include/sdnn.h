@@ -62,9 +62,11 @@ typedef enum {
  *                 times, with panels of 4, 12, 8 and 16 rows, and a fifth time with 32-row
  *                 panels for 128-column tiles unless tile_cols = 256; with tile_cols
  *                 and grouping 0 too (a default plan), also for the row-quad kernel, which
- *                 then serves sdnn_spmm and sdnn_conv3x3 (same result bit for bit; products
- *                 unless sdnn_plan_tune measured the panel kernel faster at N).  The panel
- *                 kernel, which serves the K-split calls and plans that fix panel_rows,
+ *                 then serves sdnn_spmm and sdnn_conv3x3 (same result bit for bit; not where
+ *                 the rows' entries lie so unevenly over K that the panel kernel is estimated
+ *                 to be as fast, nor products at an N where sdnn_plan_tune measured it
+ *                 faster; sdnn_plan_launch_quads reports which).  The panel kernel, which also
+ *                 serves the K-split calls and plans that fix panel_rows,
  *                 grouping or tile_cols, picks one packing per call: the 32-row panels (with 12
  *                 consumer waves per workgroup) when W holds under 20 entries per 16 rows
  *                 and 32 columns and their grid fills the compute units; otherwise the

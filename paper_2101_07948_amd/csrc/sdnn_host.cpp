@@ -1068,7 +1068,9 @@ sdnn_status sdnn_plan_create(const int32_t* row_ptr, const int32_t* col_idx, con
         d.cap = Q.cap;
         d.nprogs = Q.nprogs;
         for (const QuadProgram& P : Q.progs) d.blocks += P.blocks;
-        d.longest = Q.nprogs > 0 ? Q.progs[0].blocks : 0;
+        quad_chains(Q, plan->K, d.chain);
+        for (int w = 1; w <= std::min(kMaxQuadWaves, Q.nprogs); ++w)
+          plan->uneven_chains |= quads_uneven(d, w, plan->nnz);
         d.stream = (const uint32_t*)put(Q.stream);
         d.descs = (const uint32_t*)put(Q.descs);
         d.progs = (const QuadProgram*)put(Q.progs);
@@ -1076,6 +1078,10 @@ sdnn_status sdnn_plan_create(const int32_t* row_ptr, const int32_t* col_idx, con
         d.outs = (const int32_t*)put(Q.outs);
       }
       plan->nquads = (int)quads.size();
+      for (size_t i = 0; i < packs.size() && plan->uneven_chains; ++i) {
+        plan->pk[i].groups = packs[i].stored / kGroup;
+        panel_chains(packs[i], plan->pk[i].chain);
+      }
       if (hipMemcpy(plan->d_mem, host.data(), (size_t)total, hipMemcpyHostToDevice) !=
           hipSuccess) {
         (void)hipGetLastError();

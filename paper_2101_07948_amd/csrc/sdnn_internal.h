@@ -107,7 +107,7 @@ constexpr int kMaxPackings = 5;
 constexpr int kQuadTileCols = 64;
 constexpr int kQuadChunk = 64, kQuadRing = 8;
 constexpr int kQuadRowBytes = 4 * kQuadTileCols;
-constexpr int kQuadProducers = 4;
+constexpr int kQuadProducers = 4, kMaxQuadWaves = 16 - kQuadProducers;  // consumer waves
 // Ring slot s at LDS address quad_slot(s): slots s and s + 4 differ in one address bit, so an
 // item whose first chunk falls on slot 4 reads the stream's addresses with that bit flipped, and
 // an item's chunks need only be rounded up to half the ring (rounded up to the ring, the 12
@@ -190,17 +190,34 @@ inline int64_t quad_max_bytes(int64_t panel_bytes) {
 bool check_quads(const int32_t* row_ptr, const int32_t* col_idx, const float* values, int32_t M,
                  int32_t K, const int32_t* out_row, const QuadPacked& Q);
 
+// The program that consumer wave `stratum` of row-block rb runs (n_rb row-blocks): the strata of
+// the list sorted by length in snake order over the row-blocks.
+inline int quad_program(int stratum, int rb, int n_rb) {
+  return stratum * n_rb + ((stratum & 1) ? n_rb - 1 - rb : rb);
+}
+// chain[w], w = 1 to kMaxQuadWaves: the blocks a workgroup of w consumer waves goes through one
+// after another (mean over a few row-blocks).  The ring couples the waves: over a span of
+// kQuadRing chunks they take as long as the slowest of them has to do there, so it is the sum over
+// the spans of the most blocks any of the waves has in it.  Uniform rows make it 1.0-1.2 times the
+// longest program; where the waves' rows have their entries in different parts of K, up to w times.
+void quad_chains(const QuadPacked& Q, int32_t K, float* chain);
+
 // One quad packing in device memory.
 struct DevQuads {
   int32_t cap = 0, nprogs = 0;
   int64_t blocks = 0;   // of all programs
-  int32_t longest = 0;  // blocks of the longest program
+  float chain[kMaxQuadWaves + 1] = {};  // quad_chains
   const uint32_t* stream = nullptr;
   const uint32_t* descs = nullptr;
   const QuadProgram* progs = nullptr;
   const int32_t* rows = nullptr;
   const int32_t* outs = nullptr;
 };
+
+// The same of a panel packing: chain[w], w = 1 to kMaxPanelWaves, in groups, over spans of kRing
+// chunks, for workgroups of w panels in workgroup order.
+constexpr int kMaxPanelWaves = 14;
+void panel_chains(const Packed& P, float* chain);
 
 // CSR validation; returns SDNN_OK or SDNN_ERR_*.
 sdnn_status validate_csr(const int32_t* row_ptr, const int32_t* col_idx, int32_t M, int32_t K);
@@ -244,6 +261,8 @@ constexpr int kTunedSlots = 8;
 struct DevPacking {
   int32_t RW = 0, npanels = 0;
   double rho = 1.0, fill = 1.0;
+  int64_t groups = 0;                     // stored groups of all panels
+  float chain[kMaxPanelWaves + 1] = {};   // panel_chains (plans with uneven_chains)
   const uint32_t* entries = nullptr;      // [2*(stored + kTailGroups*kGroup)] dwords
   const uint32_t* entries_n = nullptr;    // the same groups for 128-column tiles (or null)
   const int32_t* panel_start = nullptr;   // [npanels] (in groups, -1: empty panel)
@@ -277,6 +296,7 @@ struct sdnn_plan_s {
   int nquads = 0;              // quad packings (default plans: panel_rows = 0, tile_cols = 0)
   sdnn::DevQuads quads[sdnn::kQuadPackings];
   int64_t quad_bytes = 0;      // of their device memory
+  bool uneven_chains = false;  // a launch of the row-quad kernel may be uneven (quads_uneven)
   sdnn::TunedShape tuned[sdnn::kTunedSlots];  // filled by sdnn_plan_tune
   int32_t ntuned = 0;
 };
@@ -316,12 +336,20 @@ hipError_t tune_spmm(sdnn_plan_s* p, const float* B, float* C, int32_t N, hipStr
 // The row-quad launch of a product at N columns (rows of the packing's largest programs and
 // consumer waves; 0 and 0 where the product runs on the panel kernel).
 void launch_quad_shape(const sdnn_plan_s* p, int32_t N, int32_t* program_rows, int32_t* waves);
-// The row-quad kernel (sdnn_quad.hip): whether it serves the plan's calls at N columns, the
-// launch it picks at N, the consumer waves a launch has, and its launch (conv_hwn: H, W and the
-// images of a 3x3 convolution whose input is B, or null).
+// The row-quad kernel (sdnn_quad.hip): whether it can serve the plan's calls at N columns, the
+// launch it picks at N with the microseconds its model gives that (0 for a forced one), the
+// consumer waves a launch has, and its launch (conv_hwn: H, W and the images of a 3x3 convolution
+// whose input is B, or null).
 int quad_waves(const sdnn_plan_s* p, const QuadCfg& cfg);
 bool quads_serve(const sdnn_plan_s* p, int32_t N);
-QuadCfg quad_shape(const sdnn_plan_s* p, const float* B, const float* C, int32_t N, bool conv);
+QuadCfg quad_shape(const sdnn_plan_s* p, const float* B, const float* C, int32_t N, bool conv, double* us);
+// Whether a workgroup's chain of blocks is far longer than a wave's share of W (32 entries a
+// block): filler, and waves that wait for one another.  Below 1.9 times the panel kernel was never
+// the faster one by more than 5 % in the measurements below on_quads; uniform rows of 2 % and more
+// have 1.0-1.6.
+inline bool quads_uneven(const DevQuads& d, int waves, int64_t nnz) {
+  return d.chain[waves] * 32.0 * d.nprogs > 1.9 * (double)nnz;
+}
 hipError_t launch_quads(const sdnn_plan_s* p, const float* B, float* C, int32_t N,
                         const float* bias, int epi, const int32_t* conv_hwn, const QuadCfg& cfg,
                         hipStream_t stream);

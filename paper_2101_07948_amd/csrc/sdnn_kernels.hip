@@ -149,6 +149,7 @@ static_assert(512 + 16 * kProducers <= kCtlWords * 4, "filler words outside the 
 static_assert(kAsmProducersN <= kProducers, "ready words overlap the progress words");
 static_assert(kProducers <= 16, "ready words overlap the progress words");
 static_assert(kAsmPoison == kPoison, "poison mismatch");
+static_assert(kAsmMaxConsumers == kMaxPanelWaves, "consumer count mismatch");
 
 // Scalar launch parameters (the pointers are separate __restrict__ kernel arguments so
 // the compiler may read them through the scalar cache).
@@ -750,6 +751,25 @@ int choose_tile(const sdnn_plan_s* p, int N, int nk = 1) {
   return choose_cfg(pk, p->num_cus, N, nk).waves <= kNarrowMaxWaves ? kNarrowTileCols : kTileCols;
 }
 
+// What an unsplit call takes on the panel kernel at its rule's launch, in microseconds, by a cost
+// model of the form of choose_quads: rounds of items over the CUs times
+//     stage * chunks + lat * chain + thr * groups of an item / 4 + store * rows, + 4.3.
+// stage: 0.28 on 128-column tiles, 0.40 on 256-column ones, 0.59 in 4-byte pieces, 0.64 of a
+// convolution; lat, thr, store: 0.0645, 0.028, 0.043 (128 columns), 0.056, 0.066, 0.062 (256).
+// Fitted to the panel kernel's times of the same 440 problems: 13 % rms error.  (Plans with
+// uneven_chains only.)
+double panel_time(const sdnn_plan_s* p, int N, bool aligned, bool conv) {
+  const int tw = narrow_allowed(p, N, aligned, conv) ? choose_tile(p, N) : kTileCols;
+  const DevPacking& pk = choose_packing(p, N, 1, tw);
+  const LaunchCfg cfg = choose_cfg(pk, p->num_cus, N, 1, tw);
+  const bool narrow = tw == kNarrowTileCols;
+  const double stage = narrow ? 0.28 : conv ? 0.64 : aligned ? 0.40 : 0.59;
+  const double groups = (double)pk.groups / pk.npanels * cfg.waves;
+  return 4.3 + rounds_of(cfg.n_tiles, pk.npanels, cfg.waves, slots_of(p->num_cus)) *
+                   (stage * p->nchunks + (narrow ? 0.0645 : 0.056) * pk.chain[cfg.waves] +
+                    (narrow ? 0.028 : 0.066) * groups / 4 + (narrow ? 0.043 : 0.062) * pk.RW * cfg.waves);
+}
+
 // tile: a tile width to use where the call allows it (0: the tuned or the rule's).
 hipError_t launch_panels(const sdnn_plan_s* p, const float* B, float* C, int32_t N,
                          const float* bias, int epi, const int32_t* conv_hwn,
@@ -884,21 +904,32 @@ void launch_shape(const sdnn_plan_s* p, int32_t N, int32_t* panel_rows, int32_t*
   *tile_cols = tw;
 }
 
-// Whether a product runs on the row-quad kernel, and its launch there.
-static bool product_on_quads(const sdnn_plan_s* p, const float* B, const float* C, int32_t N, QuadCfg* cfg) {
+// Whether an unsplit call runs on the row-quad kernel, and its launch there: the launch
+// sdnn_plan_tune recorded for a product, else choose_quads's, unless its chain of blocks is uneven
+// and the panel kernel, whose waves hold fewer rows, is estimated to be as fast.  Rows with their
+// entries in different parts of K (banded matrices, dense blocks) cost the row-quad kernel filler
+// and its waves a wait for one another: 4096 x 4096 with 82 neighbouring entries a row, N = 2048:
+// 199 us against 75 us on the panel kernel, 309 against 111 with the rows shuffled, 265 against 90
+// with random blocks of 64.  Of the 440 problems of the models, 46 took more than 5 % longer than on
+// the panel kernel, up to 2.8 times; with this rule 11 do, up to 1.33 times (327 x 5632 in blocks of
+// 8, 2309 x 2112 in scattered windows of 211: the model takes 25 % off the row-quad kernel's time).
+static bool on_quads(const sdnn_plan_s* p, const float* B, const float* C, int32_t N, bool conv, QuadCfg* cfg) {
   if (!quads_serve(p, N)) return false;
-  for (int i = 0; i < p->ntuned; ++i)
+  for (int i = 0; i < p->ntuned && !conv; ++i)
     if (p->tuned[i].N == N) {
       *cfg = p->tuned[i].quad;
       return p->tuned[i].quads != 0;
     }
-  *cfg = quad_shape(p, B, C, N, false);
-  return true;
+  double us = 0.0;
+  *cfg = quad_shape(p, B, C, N, conv, &us);
+  if (!p->uneven_chains || us == 0.0 || !quads_uneven(p->quads[cfg->pack], quad_waves(p, *cfg), p->nnz)) return true;
+  const bool aligned = N % 4 == 0 && (((uintptr_t)B | (uintptr_t)C) & 15) == 0;
+  return panel_time(p, N, aligned, conv) >= 1.05 * us;
 }
 
 void launch_quad_shape(const sdnn_plan_s* p, int32_t N, int32_t* program_rows, int32_t* waves) {
   QuadCfg cfg;
-  const bool quads = product_on_quads(p, nullptr, nullptr, N, &cfg);
+  const bool quads = on_quads(p, nullptr, nullptr, N, false, &cfg);
   *program_rows = quads ? 4 * p->quads[cfg.pack].cap : 0;
   *waves = quads ? quad_waves(p, cfg) : 0;
 }
@@ -906,7 +937,7 @@ void launch_quad_shape(const sdnn_plan_s* p, int32_t N, int32_t* program_rows, i
 hipError_t launch_spmm(const sdnn_plan_s* p, const float* B, float* C, int32_t N,
                        const float* bias, int epi, hipStream_t stream) {
   QuadCfg cfg;
-  if (product_on_quads(p, B, C, N, &cfg)) return launch_quads(p, B, C, N, bias, epi, nullptr, cfg, stream);
+  if (on_quads(p, B, C, N, false, &cfg)) return launch_quads(p, B, C, N, bias, epi, nullptr, cfg, stream);
   return launch_panels(p, B, C, N, bias, epi, nullptr, nullptr, nullptr, 0, stream);
 }
 
@@ -972,7 +1003,8 @@ hipError_t tune_spmm(sdnn_plan_s* p, const float* B, float* C, int32_t N, hipStr
   // the row-quad kernel, where it serves the call: every packing with its most consumer waves
   // and three smaller counts, and the cost model's choice
   if (err == hipSuccess && quads_serve(p, N)) {
-    std::vector<QuadCfg> quads{quad_shape(p, B, C, N, false)};
+    double us;
+    std::vector<QuadCfg> quads{quad_shape(p, B, C, N, false, &us)};
     for (int k = 0; k < p->nquads; ++k)
       for (int w : {12, 9, 6, 3})
         if (w <= std::max(3, p->quads[k].nprogs)) quads.push_back(QuadCfg{k, w});
@@ -1089,8 +1121,9 @@ hipError_t scratch_address(int device, float** out) {
 hipError_t launch_conv3x3(const sdnn_plan_s* p, const float* X, float* C, int32_t H, int32_t W,
                           int32_t NB, const float* bias, int epi, hipStream_t stream) {
   const int32_t hwn[3] = {H, W, NB};
-  if (quads_serve(p, H * W * NB))
-    return launch_quads(p, X, C, H * W * NB, bias, epi, hwn, quad_shape(p, X, C, H * W * NB, true), stream);
+  QuadCfg cfg;
+  if (on_quads(p, X, C, H * W * NB, true, &cfg))
+    return launch_quads(p, X, C, H * W * NB, bias, epi, hwn, cfg, stream);
   return launch_panels(p, X, C, H * W * NB, bias, epi, hwn, nullptr, nullptr, 0, stream);
 }
 

@@ -71,7 +71,6 @@ constexpr int kPollBudgetQuad = 1 << 22;
 constexpr int kCtl = kQuadZeroRow + kQuadRowBytes;
 constexpr int kLdsBytes = (kQuadZeroRow | kQuadFlip) + kQuadRowBytes;
 static_assert(kCtl + 256 <= (kQuadZeroRow | kQuadFlip) && kLdsBytes <= 160 * 1024, "LDS layout");
-constexpr int kMaxQuadConsumers = 16 - kQuadProducers;
 
 struct QuadArgs {
   int32_t K, N, nchunks, nprogs;
@@ -348,7 +347,7 @@ struct QuadCursor {
   __device__ __forceinline__ void find(const QuadArgs& a) {  // the program of `item`
     tile = item / a.n_rb;
     const int rb = item - tile * a.n_rb;
-    prog = stratum * a.n_rb + ((stratum & 1) ? a.n_rb - 1 - rb : rb);
+    prog = stratum * a.n_rb + ((stratum & 1) ? a.n_rb - 1 - rb : rb);  // quad_program
   }
   __device__ __forceinline__ bool next(const QuadArgs& a) {
     item += a.total_wg;
@@ -530,45 +529,46 @@ int env_or(const char* name, int dflt) {
 
 // The packing and the consumer waves of a call: those that a cost model gives the least
 // time.  In microseconds, for a workgroup's item (all measured on MI355X):
-//     lat * (longest + mean program)/2 + thr * mean * max(waves / 4, 1)   blocks of 8 quad-steps
-//   + sync * chunks + stage * ring chunks                                 handshakes, staging
-//   + store * rows + item                                                 epilogue, start
-// times the rounds of items over the CUs.  lat, thr, sync, item: 0.073, 0.040, 0.147, 0.23 for
-// programs of 4 and 8 rows, 0.105, 0.015, 0.053, 0.26 (0.93) for those of 16 (32); stage: 0.13,
-// 4-byte pieces 0.20, a convolution 0.21; store: 0.0039 (32 rows 0.0033).  Fitted to 4900 timings
-// over 131 problems (M, K = 100 to 3072, 3 to 30 % dense, N = 32 to 16384, uniform and lognormal
-// rows, ragged N, convolutions): 9 % rms error.  Over 215 problems, those with K = 32 to 200
-// included, the pick's time is within 2 % of the fastest candidate's on average (20 % at worst),
-// the noise of the single timings included.  Programs of 32 rows, streamed, only from 8 chunks of
+//     lat * chain + thr * mean program * max(waves / 4, 1)   blocks of 8 quad-steps
+//   + sync * chunks + stage * ring chunks                    handshakes, staging
+//   + store * rows + item                                    epilogue, start
+// times the rounds of items over the CUs, + 3.5 for the launch.  lat, thr, sync, item: 0.080, 0.039,
+// 0.082, 0.21 for programs of 4 and 8 rows, 0.112, 0.016, 0.074, 0.17 (0.58) for those of 16 (32);
+// stage: 0.13, 4-byte pieces 0.29, a convolution 0.20; store: 0.0071 (32 rows 0.0054), a third more
+// through the caches.  Fitted to 12900 timings over 440 problems (M = 16 to 4096, K = 24 to 6100, 0.4
+// to 40 % dense, N = 16 to 33000; uniform, lognormal, banded and block-structured rows, ragged N,
+// convolutions): 12 % rms error (18 % with the longest program in place of the chain).  The pick's
+// time is within 1-2 % of the fastest candidate's on average (22 % at worst, of banded rows), the
+// noise of the single timings included.  Programs of 32 rows, streamed, only from 8 chunks of
 // K up: below, their bursts of stores are what is waited for (1500 x 100 at 90 %, N = 16384: 34.8
 // against 30.8 us with 16-row ones).
-QuadCfg choose_quads(const sdnn_plan_s* p, int N, QuadStage stage, bool cached) {
+QuadCfg choose_quads(const sdnn_plan_s* p, int N, QuadStage stage, bool cached, double* us) {
   const int64_t tiles = (N + kQuadTileCols - 1) / kQuadTileCols;
   const uint32_t cus = p->num_cus > 0 ? p->num_cus : 256;
   const int chunks = (p->K + kQuadChunk - 1) / kQuadChunk;
-  const double t_stage = stage == kQuadVec ? 0.13 : stage == kQuadDword ? 0.20 : 0.21;
+  const double t_stage = stage == kQuadVec ? 0.13 : stage == kQuadDword ? 0.29 : 0.20;
   QuadCfg best{0, 1};
   double best_t = -1.0;
   for (int i = 0; i < p->nquads; ++i) {
     const DevQuads& d = p->quads[i];
     if (d.cap == 8 && chunks < 8 && !cached) continue;
     const bool wide = d.cap <= 2;
-    const double mean = (double)d.blocks / d.nprogs;
-    const double fixed = (wide ? 0.073 : 0.105) * 0.5 * (mean + d.longest) +
-                         (wide ? 0.147 : 0.053) * chunks + (wide ? 0.23 : d.cap == 4 ? 0.26 : 0.93);
-    for (int w = std::min(2, d.nprogs); w <= std::min(kMaxQuadConsumers, d.nprogs); ++w) {
+    const double lat = wide ? 0.080 : 0.112, thr = (wide ? 0.039 : 0.016) * (double)d.blocks / d.nprogs;
+    const double fixed = (wide ? 0.082 : 0.074) * chunks + (wide ? 0.21 : d.cap == 4 ? 0.17 : 0.58);
+    const double store = (d.cap == 8 ? 0.0054 : 0.0071) * (cached ? 1.33 : 1.0) * 4.0 * d.cap;
+    for (int w = 1; w <= std::min(kMaxQuadWaves, d.nprogs); ++w) {
       const int64_t items = tiles * ((d.nprogs + w - 1) / w);
       // (the loop is host time of every call: 32-bit divisions where they do)
       const int64_t rounds = items < (int64_t)1 << 31 ? ((uint32_t)items + cus - 1) / cus : (items + cus - 1) / cus;
       const int staged = rounds > 1 ? (chunks + 3) / 4 * 4 : chunks;
-      const double t = rounds * (fixed + (wide ? 0.040 : 0.015) * mean * std::max(0.25 * w, 1.0) +
-                                 t_stage * staged + (d.cap == 8 ? 0.0033 : 0.0039) * 4.0 * d.cap * w);
+      const double t = rounds * (lat * d.chain[w] + thr * std::max(0.25 * w, 1.0) + fixed + t_stage * staged + store * w);
       if (best_t < 0.0 || t < best_t) {
         best_t = t;
         best = QuadCfg{i, w};
       }
     }
   }
+  *us = best_t + 3.5;
   return best;
 }
 
@@ -585,17 +585,18 @@ static QuadStage quad_stage(const float* B, const float* C, int32_t N) {
   return N % 4 == 0 && (((uintptr_t)B | (uintptr_t)C) & 15) == 0 ? kQuadVec : kQuadDword;
 }
 
-QuadCfg quad_shape(const sdnn_plan_s* p, const float* B, const float* C, int32_t N, bool conv) {
-  QuadCfg c = choose_quads(p, N, conv ? kQuadConv : quad_stage(B, C, N), cached_stores(p, C, N));
+QuadCfg quad_shape(const sdnn_plan_s* p, const float* B, const float* C, int32_t N, bool conv, double* us) {
+  QuadCfg c = choose_quads(p, N, conv ? kQuadConv : quad_stage(B, C, N), cached_stores(p, C, N), us);
   const int cap = env_or("SDNN_FORCE_QUAD_CAP", 0), waves = env_or("SDNN_FORCE_QUAD_WAVES", 0);  // tests
   for (int i = 0; i < p->nquads; ++i)
     if (p->quads[i].cap == cap) c.pack = i;
   if (waves > 0) c.waves = waves;
+  if (cap > 0 || waves > 0) *us = 0.0;
   return c;
 }
 
 int quad_waves(const sdnn_plan_s* p, const QuadCfg& cfg) {
-  return std::max(1, std::min({cfg.waves, kMaxQuadConsumers, p->quads[cfg.pack].nprogs}));
+  return std::max(1, std::min({cfg.waves, kMaxQuadWaves, p->quads[cfg.pack].nprogs}));
 }
 
 hipError_t launch_quads(const sdnn_plan_s* p, const float* B, float* C, int32_t N,

@@ -136,6 +136,55 @@ bool pack_quads(const int32_t* row_ptr, const int32_t* col_idx, const float* val
   return true;
 }
 
+void quad_chains(const QuadPacked& Q, int32_t K, float* chain) {
+  const int spans = std::max(0, K - 1) / (kQuadChunk * kQuadRing) + 1;
+  std::vector<int32_t> most(spans), own(spans);
+  for (int w = 1; w <= kMaxQuadWaves; ++w) {
+    const int n_rb = (Q.nprogs + w - 1) / w, step = std::max(1, n_rb / 4);
+    double sum = 0.0;
+    int looked_at = 0;
+    for (int rb = 0; rb < n_rb; rb += step, ++looked_at) {
+      std::fill(most.begin(), most.end(), 0);
+      for (int s = 0; s < w; ++s) {
+        const int p = quad_program(s, rb, n_rb);
+        if (p >= Q.nprogs || Q.progs[p].start < 0) continue;
+        std::fill(own.begin(), own.end(), 0);
+        for (size_t d = (size_t)Q.progs[p].desc; Q.descs[d] != 0; ++d)
+          if (Q.descs[d] != kQuadMoreDescs)
+            own[(Q.descs[d] >> kQuadLoShift & kQuadLoMask) / kQuadRing] += (int32_t)(Q.descs[d] & kQuadMaxBlocks);
+        for (int b = 0; b < spans; ++b) most[b] = std::max(most[b], own[b]);
+      }
+      for (int b = 0; b < spans; ++b) sum += most[b];
+    }
+    chain[w] = looked_at ? (float)(sum / looked_at) : 0.0f;
+  }
+}
+
+void panel_chains(const Packed& P, float* chain) {
+  const int spans = std::max(1, (P.nchunks + kRing - 1) / kRing);
+  std::vector<int32_t> most(spans), own(spans);
+  for (int w = 1; w <= kMaxPanelWaves; ++w) {
+    const int n_rb = (P.npanels + w - 1) / w, step = std::max(1, n_rb / 4);
+    double sum = 0.0;
+    int looked_at = 0;
+    for (int rb = 0; rb < n_rb; rb += step, ++looked_at) {
+      std::fill(most.begin(), most.end(), 0);
+      for (int j = rb * w; j < std::min((rb + 1) * w, P.npanels); ++j) {
+        const int32_t first = P.panel_start[P.panel_order[j]];
+        if (first < 0) continue;
+        std::fill(own.begin(), own.end(), 0);
+        for (const uint32_t* a = &P.entries[(size_t)first * 2 * kGroup + kGroup];; a += 2 * kGroup) {
+          ++own[(a[kLoWord] >> kLoShift) / kRing];
+          if (a[kHiWord] >> kEndBit & 1u) break;
+        }
+        for (int b = 0; b < spans; ++b) most[b] = std::max(most[b], own[b]);
+      }
+      for (int b = 0; b < spans; ++b) sum += most[b];
+    }
+    chain[w] = looked_at ? (float)(sum / looked_at) : 0.0f;
+  }
+}
+
 bool check_quads(const int32_t* row_ptr, const int32_t* col_idx, const float* values, int32_t M,
                  int32_t K, const int32_t* out_row, const QuadPacked& Q) {
   const uint32_t last_chunk = (uint32_t)std::max(0, (K - 1) / kQuadChunk);

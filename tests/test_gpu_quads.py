@@ -295,3 +295,52 @@ def test_tuned_launch_is_the_one_calls_run_on():
         got = plan.launch_quads(784)
         assert got is None or got == rule or got["waves"] in (3, 6, 9, 12)
         assert np.array_equal(run(plan, B, None, "none"), run(panel, B, None, "none"))
+
+
+def uneven_rows(kind, M, K, n, seed):
+    """M rows of n entries that lie together: along the diagonal, at random places, or in random
+    blocks of 64 columns."""
+    rng = np.random.default_rng(seed)
+    if kind == "blocks":
+        cols = np.stack([np.sort(rng.choice(K // 64, n // 64, replace=False)) for _ in range(M)])
+        cols = (64 * cols[:, :, None] + np.arange(64)).reshape(M, -1)
+    else:
+        start = np.arange(M) * (K - n) // (M - 1)
+        cols = (start if kind == "band" else rng.permutation(start))[:, None] + np.arange(n)
+    n = cols.shape[1]
+    values = rng.standard_normal(M * n).astype(np.float32)
+    return inputs.CSR(np.arange(0, M * n + 1, n, dtype=np.int32), cols.astype(np.int32).ravel(), values, M, K)
+
+
+@pytest.mark.parametrize("kind", ["band", "runs", "blocks"])
+def test_uneven_rows_run_on_the_panel_kernel(kind):
+    """Rows whose entries lie in different parts of K leave the row-quad kernel filler and waves that
+    wait for one another: where there are many of them (4096 x 4096, 2 %, N = 2048: 2.6 to 3 times
+    slower there) products run on the panel kernel, uniform rows stay.  Small and ragged shapes of
+    the same patterns agree with the oracle on whichever kernel the rule takes."""
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        with sd.Plan.from_csr(uneven_rows(kind, 4096, 4096, 82 if kind != "blocks" else 64, 7900)) as plan:
+            assert plan.launch_quads(2048) is None
+        with sd.Plan.from_csr(inputs.pattern_uniform(4096, 4096, 0.02, inputs.CFG_TEST, 7901, 0.05)) as plan:
+            assert plan.launch_quads(2048) is not None
+    for M, K, n, N in ((300, 2048, 64, 516), (1000, 1024, 128, 1023), (65, 4096, 64, 4096)):
+        check(uneven_rows(kind, M, K, n, 7910 + M), N, f"{kind} M {M}", "relu")
+        check(uneven_rows(kind, M, K, n, 7910 + M), N, f"{kind} M {M} permuted", out_permuted=True)
+
+
+def test_uneven_filters_convolve(force):
+    """The same rule of convolutions: block-structured filters, on both kernels."""
+    F = uneven_rows("blocks", 128, 576, 64, 7950)
+    X = torch.from_numpy(np.random.default_rng(7951).standard_normal((64, 28, 28, 8)).astype(np.float32)).to(DEV)
+    out = []
+    for forced in (False, True):
+        if forced:
+            force(4, 6)
+        with sd.Plan.from_csr(F) as plan:
+            C = torch.full((128, 28, 28, 8), float("nan"), device=DEV)
+            plan.conv3x3(X, C, None, "relu")
+            torch.cuda.synchronize()
+            out.append(C.cpu().numpy())
+    ref, bound = oracle.conv3x3_f64(F.row_ptr, F.col_idx, F.values, X.cpu().numpy(), None, "relu")
+    assert (np.abs(out[0].astype(np.float64) - ref) <= tol_fp32(bound, "relu")).all()
+    assert np.array_equal(out[0], out[1])
