@@ -95,6 +95,7 @@ TOUCH_AHEAD = 512  # bytes of stream pulled into L2 ahead of the scalar ring
 GROUP_BYTES = 8 * G
 INF = 0x7FFFFFFF
 POISON = 0x7FC0DEAD
+BUDGET_AT = 128          # a consumer's poll budget: LDS word at its progress word + BUDGET_AT
 MAX_CONS = 14      # consumer waves a workgroup can have
 PROFILE = False    # scratch builds only: time consumers spend waiting (%[twait])
 
@@ -237,7 +238,7 @@ def consumer(rw, limit=False, lay=WIDE):
         f"v_mov_b32 v31, {hex(lay.RING_MASK)}",
         "v_mov_b32 v28, 0",
         f"s_mov_b32 s{SREADY}, 0",
-        f"s_mov_b32 s{SPOLL}, %[budget]",
+        f"ds_read_b32 v30, %[pa] offset:{BUDGET_AT}",
     ]
     if PROFILE:
         L.append("s_mov_b32 %[twait], 0")
@@ -248,6 +249,7 @@ def consumer(rw, limit=False, lay=WIDE):
         f"s_add_u32 s{PTR}, s{PTR}, {GROUP_BYTES * (NSLOT - 1)}",
         f"s_addc_u32 s{PTR + 1}, s{PTR + 1}, 0",
         "s_waitcnt lgkmcnt(0)",
+        f"v_readfirstlane_b32 s{SPOLL}, v30",
     ]
     L += sync(E[0], "e", lay)   # a panel's first group always carries the sync bit
     L += address_phase(E[0], VB[0], lay)
@@ -298,9 +300,11 @@ def consumer(rw, limit=False, lay=WIDE):
           f"s_cmp_eq_u32 s{STMP}, 0", "s_cbranch_scc1 .L%=_clean",
           ".L%=_poison:"]
     L += [f"v_mov_b32 v{ACC + x}, {hex(POISON)}" for x in range(V * rw)]
-    L += [".L%=_clean:", "v_mov_b32 v30, %[next]"]
+    L += [".L%=_clean:", f"v_mov_b32 v30, s{SPOLL}"]
+    L += lane0_write("%[pa]", f"v30 offset:{BUDGET_AT}", lay)
+    L.append("v_mov_b32 v30, %[next]")
     L += lane0_write("%[pa]", "v30", lay)
-    L += ["s_waitcnt vmcnt(0) lgkmcnt(0)", f"s_mov_b32 %[budget], s{SPOLL}", f"s_mov_b32 m0, s{M0S}"]
+    L += ["s_waitcnt vmcnt(0) lgkmcnt(0)", f"s_mov_b32 m0, s{M0S}"]
     body = "\n".join('      "' + x + '\\n\\t"' for x in L)
     planes = ", ".join(f'"+{{v[{ACC + k * rw}:{ACC + k * rw + rw - 1}]}}"(p{k})' for k in range(V))
     lo, hi = min(E[0], PTR), max(E[-1] + 2 * G - 1, lay.SREADY1)
@@ -319,7 +323,7 @@ __device__ __forceinline__ void {name}({params},
     ConsumerArgs& a) {{
   asm volatile(
 {body}
-      : {planes}, [budget] "+s"(a.poll_budget){', [twait] "=&s"(a.twait)' if PROFILE else ''}
+      : {planes}{', [twait] "=&s"(a.twait)' if PROFILE else ''}
       : {operands}
       : {clob});
 }}
@@ -747,7 +751,7 @@ def generate() -> str:
              f"constexpr int kAsmProducersN = {NARROW.NPROD}, kAsmTileBytesN = {NARROW.ROW_BYTES};",
              f"constexpr int kAsmAccBaseN = {NARROW.ACC}, kAsmEndBitN = {NARROW.END_BIT};",
              f"constexpr uint32_t kAsmRingMaskN = {hex(NARROW.RING_MASK)}u;",
-             f"constexpr uint32_t kProgressDone = {hex(INF)}u, kAsmPoison = {hex(POISON)}u;",
+             f"constexpr uint32_t kProgressDone = {hex(INF)}u, kAsmPoison = {hex(POISON)}u, kAsmBudgetAt = {BUDGET_AT};",
              ""]
     for rw in RW_VARIANTS:
         parts.append(consumer(rw))

@@ -56,7 +56,6 @@ struct ConsumerArgs {
   uint32_t vlane;          // 16 * lane: the lane's byte offset in a staged B row
   uint32_t prog_addr;      // LDS address of this consumer's progress word
   uint32_t ready_addr;     // LDS address of the ready word
-  uint32_t poll_budget;    // failed readiness checks the wave may still poll through (all items)
   uint32_t overrun_addr;   // LDS address of the workgroup's overrun word
   uint32_t chunk_limit;    // the wave stops before a sync group whose c_lo reaches this chunk
   uint32_t chunk_base;     // ring chunk number of the item's chunk 0 (added to c_lo, c_hi)
@@ -142,7 +141,8 @@ constexpr int threads_of() { return TW == kTileCols ? max_threads<RW>() : narrow
 template <int RW, int TW>
 constexpr int min_waves_of() { return TW == kTileCols ? 1 : narrow_waves_per_simd<RW>(); }
 // LDS control words after the ring: ready[kProducers] at +0, progress[16] at +64, the
-// overrun word at +128 (nonzero once a producer staged past the ring limit), and 16
+// overrun word at +128 (nonzero once a producer staged past the ring limit), the consumers'
+// poll budgets[16] at +192 (what each may still poll through, over all its items), and 16
 // bytes per producer at +512 that the convolution producer's filler loads write.
 constexpr int kCtlWords = 256;
 static_assert(512 + 16 * kProducers <= kCtlWords * 4, "filler words outside the control area");
@@ -231,6 +231,7 @@ __global__ __launch_bounds__((threads_of<RW, TW>()), (min_waves_of<RW, TW>())) v
     if (prod == 0 && lane >= nc && lane < 16) ctl[16 + lane] = kProgressDone;  // absent consumers
   } else if (lane == 0) {
     ctl[16 + wave] = (uint32_t)c0;  // reads the first item from its first chunk on
+    ctl[16 + kAsmBudgetAt / 4 + wave] = a.poll_budget;
   }
   __syncthreads();
 
@@ -291,7 +292,6 @@ __global__ __launch_bounds__((threads_of<RW, TW>()), (min_waves_of<RW, TW>())) v
     return;
   }
 
-  uint32_t budget = a.poll_budget;
   for (int it = 0; it < nitems; ++it) {
     int tile = tile0, rb = g + it * a.wg_per_tile;
     if (a.tile_major) {
@@ -323,7 +323,6 @@ __global__ __launch_bounds__((threads_of<RW, TW>()), (min_waves_of<RW, TW>())) v
       ca.vlane = (uint32_t)lane * (4u * V);
       ca.prog_addr = prog0 + 4u * (uint32_t)wave;
       ca.ready_addr = ready_addr;
-      ca.poll_budget = budget;
       ca.overrun_addr = overrun_addr;
       ca.chunk_limit = (uint32_t)c1;
       ca.chunk_base = cbase;
@@ -353,7 +352,6 @@ __global__ __launch_bounds__((threads_of<RW, TW>()), (min_waves_of<RW, TW>())) v
         if constexpr (RW == 12) consume_rw12(p0, p1, p2, p3, ca);
         if constexpr (RW == 16) consume_rw16(p0, p1, p2, p3, ca);
       }
-      budget = ca.poll_budget;
     } else if (lane == 0) {
       ctl[16 + wave] = next;  // nothing to read in this row-block
     }
@@ -659,30 +657,31 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
     const int32_t n = (int32_t)(q - (int64_t)i * nq) * 4;
     const int64_t at = (int64_t)i * N + n;
     const float bb = bias ? bias[rowmap ? rowmap[i] : i] : 0.0f;
+    // a run that left kPoison there makes the sum NaN, which no activation may hide
+    auto spent = [&](float acc, int64_t where) {
+      bool found = false;
+      if (acc != acc)
+        for (int s = 0; s < nseg; ++s) found |= __float_as_uint(ws[s * plane + where]) == kPoison;
+      return found;
+    };
     if (VEC) {
       float4 acc = *reinterpret_cast<const float4*>(ws + at);
-      bool spent = __float_as_uint(acc.x) == kPoison;  // (a wave's columns come in fours)
       for (int s = 1; s < nseg; ++s) {
         const float4 v = *reinterpret_cast<const float4*>(ws + s * plane + at);
-        spent |= __float_as_uint(v.x) == kPoison;
         acc.x += v.x;
         acc.y += v.y;
         acc.z += v.z;
         acc.w += v.w;
       }
-      const int act = spent ? (int)SDNN_EPI_NONE : epi;  // (the sums are NaN)
-      store_c4(C + at, activation(acc.x + bb, act), activation(acc.y + bb, act),
-               activation(acc.z + bb, act), activation(acc.w + bb, act));
+      float4 out = {activation(acc.x + bb, epi), activation(acc.y + bb, epi),
+                    activation(acc.z + bb, epi), activation(acc.w + bb, epi)};
+      if (spent(acc.x, at)) out = acc;  // (a wave's columns come in fours)
+      store_c4(C + at, out.x, out.y, out.z, out.w);
     } else {
       for (int c = 0; c < 4 && n + c < N; ++c) {
         float acc = ws[at + c];
-        bool spent = __float_as_uint(acc) == kPoison;
-        for (int s = 1; s < nseg; ++s) {
-          const float v = ws[s * plane + at + c];
-          spent |= __float_as_uint(v) == kPoison;
-          acc += v;
-        }
-        store_c1(C + at + c, activation(acc + bb, spent ? (int)SDNN_EPI_NONE : epi));
+        for (int s = 1; s < nseg; ++s) acc += ws[s * plane + at + c];
+        store_c1(C + at + c, spent(acc, at + c) ? acc : activation(acc + bb, epi));
       }
     }
   }

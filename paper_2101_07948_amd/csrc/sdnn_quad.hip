@@ -359,7 +359,7 @@ struct QuadCursor {
 // divide the workgroups, all of the wave's): its loop and the epilogue of its rows per item.
 // The rows' tables are read once; read per item, their two dependent loads stood between the
 // items of every wave.
-template <int NS, int STAGE>
+template <int CAP, int NS, int STAGE>
 __device__ __forceinline__ void run_program(QuadConsumer& ca, bool entries, const int32_t* rows,
                                             const int32_t* outs, float* C, const float* bias,
                                             QuadCursor& cur, int lane, const QuadArgs& a) {
@@ -390,6 +390,9 @@ __device__ __forceinline__ void run_program(QuadConsumer& ca, bool entries, cons
       if constexpr (NS == 2) consume_quads2(acc, ca);
       if constexpr (NS == 4) consume_quads4(acc, ca);
       if constexpr (NS == 8) consume_quads8(acc, ca);
+      // (between the loops the budget is in a VGPR: SGPRs are short and spill; but for the packing
+      // of 32-row programs, whose VGPRs are)
+      if constexpr (CAP == 8) ca.poll_budget = __builtin_amdgcn_readfirstlane(ca.poll_budget);
     } else if (lane == 0) {
       lds_write(ca.prog_addr, ca.next_progress);  // no entries: only epi(bias)
     }
@@ -479,10 +482,10 @@ __global__ __launch_bounds__(1024) void spmm_quad_kernel(
     ca.poll_budget = budget;
     const int32_t* r = rows + (size_t)cur.prog * (4 * CAP);
     const int32_t* o = outs + (size_t)cur.prog * (4 * CAP);
-    if (CAP == 8 && P.NS == 8) run_program<8, STAGE>(ca, P.start >= 0, r, o, C, bias, cur, lane, a);
-    else if (CAP >= 4 && P.NS == 4) run_program<4, STAGE>(ca, P.start >= 0, r, o, C, bias, cur, lane, a);
-    else if (CAP >= 2 && P.NS == 2) run_program<2, STAGE>(ca, P.start >= 0, r, o, C, bias, cur, lane, a);
-    else run_program<1, STAGE>(ca, P.start >= 0, r, o, C, bias, cur, lane, a);
+    if (CAP == 8 && P.NS == 8) run_program<CAP, 8, STAGE>(ca, P.start >= 0, r, o, C, bias, cur, lane, a);
+    else if (CAP >= 4 && P.NS == 4) run_program<CAP, 4, STAGE>(ca, P.start >= 0, r, o, C, bias, cur, lane, a);
+    else if (CAP >= 2 && P.NS == 2) run_program<CAP, 2, STAGE>(ca, P.start >= 0, r, o, C, bias, cur, lane, a);
+    else run_program<CAP, 1, STAGE>(ca, P.start >= 0, r, o, C, bias, cur, lane, a);
     budget = ca.poll_budget;
   }
 }
