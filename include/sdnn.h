@@ -315,7 +315,9 @@ sdnn_status sdnn_plan_launch_tile(sdnn_plan p, int32_t N, int32_t* tile_cols);
  * each tile width the call allows (256 and 128 columns, see tile_cols), and for every
  * row-quad packing a default plan holds, on the caller's B (K x N) and C (M x N,
  * overwritten with unspecified values), and records the fastest of each kernel in the plan;
- * later sdnn_spmm calls with the same N use the faster one (up to 8 N values are kept).  For
+ * later sdnn_spmm calls with the same N use the faster one (up to 8 N values are kept; the
+ * choice between the kernels and the row-quad launch only where B and C are aligned as the
+ * timed ones: other calls take the library's).  For
  * a plan with K-segments it then times sdnn_spmm_split at every workgroup count along K
  * (up to 32) in a workspace it allocates for the search and frees (skipped if that
  * allocation fails), and records the fastest, one meaning the unsplit call, for

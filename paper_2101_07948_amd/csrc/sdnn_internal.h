@@ -249,10 +249,12 @@ struct QuadCfg {
 // A launch shape sdnn_plan_tune measured fastest for one N: which packing, how many
 // consumer waves per workgroup and which tile width; and, for plans with K-segments, the
 // workgroups along K and the tile width of the fastest K-split call (0: not measured).  The
-// panel shape is recorded also where the row-quad kernel was faster.
+// panel shape is recorded also where the row-quad kernel was faster.  Which kernel was, and its
+// launch, hold for calls that stage B and store C as the timed ones did (quad_access).
 struct TunedShape {
   int32_t N = 0, pack = 0, waves = 0, tile = 256, splits = 0, split_tile = 0;
   int32_t quads = 0;  // the row-quad launch `quad` was faster than the panel shape
+  int32_t access = 0;  // quad_access of the timed B and C
   QuadCfg quad;
 };
 constexpr int kTunedSlots = 8;
@@ -341,6 +343,9 @@ void launch_quad_shape(const sdnn_plan_s* p, int32_t N, int32_t* program_rows, i
 // consumer waves a launch has, and its launch (conv_hwn: H, W and the images of a 3x3 convolution
 // whose input is B, or null).
 int quad_waves(const sdnn_plan_s* p, const QuadCfg& cfg);
+// How the kernel reads B and writes C (16- or 4-byte pieces, streamed or through the caches),
+// which their alignment decides.
+int quad_access(const sdnn_plan_s* p, const float* B, const float* C, int32_t N);
 bool quads_serve(const sdnn_plan_s* p, int32_t N);
 QuadCfg quad_shape(const sdnn_plan_s* p, const float* B, const float* C, int32_t N, bool conv, double* us);
 // Whether a workgroup's chain of blocks is far longer than a wave's share of W (32 entries a

@@ -903,8 +903,8 @@ void launch_shape(const sdnn_plan_s* p, int32_t N, int32_t* panel_rows, int32_t*
   *tile_cols = tw;
 }
 
-// Whether an unsplit call runs on the row-quad kernel, and its launch there: the launch
-// sdnn_plan_tune recorded for a product, else choose_quads's, unless its chain of blocks is uneven
+// Whether an unsplit call runs on the row-quad kernel, and its launch there: what sdnn_plan_tune
+// recorded for a product of the same alignment, else choose_quads's, unless its chain of blocks is uneven
 // and the panel kernel, whose waves hold fewer rows, is estimated to be as fast.  Rows with their
 // entries in different parts of K (banded matrices, dense blocks) cost the row-quad kernel filler
 // and its waves a wait for one another: 4096 x 4096 with 82 neighbouring entries a row, N = 2048:
@@ -915,7 +915,7 @@ void launch_shape(const sdnn_plan_s* p, int32_t N, int32_t* panel_rows, int32_t*
 static bool on_quads(const sdnn_plan_s* p, const float* B, const float* C, int32_t N, bool conv, QuadCfg* cfg) {
   if (!quads_serve(p, N)) return false;
   for (int i = 0; i < p->ntuned && !conv; ++i)
-    if (p->tuned[i].N == N) {
+    if (p->tuned[i].N == N && p->tuned[i].access == quad_access(p, B, C, N)) {
       *cfg = p->tuned[i].quad;
       return p->tuned[i].quads != 0;
     }
@@ -1034,6 +1034,7 @@ hipError_t tune_spmm(sdnn_plan_s* p, const float* B, float* C, int32_t N, hipStr
       if (p->tuned[i].N == N) slot = i;
     if (slot < 0) slot = p->ntuned < kTunedSlots ? p->ntuned++ : (int)(N % kTunedSlots);
     chosen->splits = 0;
+    chosen->access = quad_access(p, B, C, N);
     p->tuned[slot] = *chosen;
   }
   // K-segmented plans: the split-K tiling factor, i.e. the workgroups along K of

@@ -588,6 +588,10 @@ static QuadStage quad_stage(const float* B, const float* C, int32_t N) {
   return N % 4 == 0 && (((uintptr_t)B | (uintptr_t)C) & 15) == 0 ? kQuadVec : kQuadDword;
 }
 
+int quad_access(const sdnn_plan_s* p, const float* B, const float* C, int32_t N) {
+  return 2 * (int)quad_stage(B, C, N) + (cached_stores(p, C, N) ? 1 : 0);
+}
+
 QuadCfg quad_shape(const sdnn_plan_s* p, const float* B, const float* C, int32_t N, bool conv, double* us) {
   QuadCfg c = choose_quads(p, N, conv ? kQuadConv : quad_stage(B, C, N), cached_stores(p, C, N), us);
   const int cap = env_or("SDNN_FORCE_QUAD_CAP", 0), waves = env_or("SDNN_FORCE_QUAD_WAVES", 0);  // tests

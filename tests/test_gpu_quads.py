@@ -297,6 +297,27 @@ def test_tuned_launch_is_the_one_calls_run_on():
         assert np.array_equal(run(plan, B, None, "none"), run(panel, B, None, "none"))
 
 
+def test_tuned_launch_is_kept_for_its_alignment():
+    """A launch timed on a B off 16 bytes (4-byte staging, C through the caches) is not taken for
+    aligned calls, whose rule picks 16-row programs and 7 waves here where that of the timed calls
+    picks 32-row ones; both kinds of calls stay right."""
+    M, K, N = 1000, 300, 3136
+    W = inputs.pattern_uniform(M, K, 0.1, inputs.CFG_TEST, 7820, 0.05)
+    flat = torch.empty(K * N + 1, device=DEV)
+    B = flat[1:].view(K, N)
+    B.copy_(torch.from_numpy(inputs.dense_B(K, N, inputs.CFG_TEST, 7821)))
+    with sd.Plan.from_csr(W) as plan, sd.Plan.from_csr(W, panel_rows=4) as panel:
+        rule = plan.launch_quads(N)
+        plan.tune(N, B, torch.empty(M, N, device=DEV))
+        assert plan.launch_quads(N) == rule
+        want = run(panel, B, None, "none")
+        assert np.array_equal(run(plan, B, None, "none"), want)
+        assert np.array_equal(run(plan, B.clone(), None, "none"), want)
+        plan.tune(N, B.clone(), torch.empty(M, N, device=DEV))  # the same N, aligned
+        assert np.array_equal(run(plan, B, None, "none"), want)
+        assert np.array_equal(run(plan, B.clone(), None, "none"), want)
+
+
 def uneven_rows(kind, M, K, n, seed):
     """M rows of n entries that lie together: along the diagonal, at random places, or in random
     blocks of 64 columns."""
