@@ -1069,6 +1069,7 @@ sdnn_status sdnn_plan_create(const int32_t* row_ptr, const int32_t* col_idx, con
         d.nprogs = Q.nprogs;
         for (const QuadProgram& P : Q.progs) d.blocks += P.blocks;
         quad_chains(Q, plan->K, d.chain);
+        quad_item_times(&d, plan->K);
         for (int w = 1; w <= std::min(kMaxQuadWaves, Q.nprogs); ++w)
           plan->uneven_chains |= quads_uneven(d, w, plan->nnz);
         d.stream = (const uint32_t*)put(Q.stream);

@@ -207,6 +207,10 @@ struct DevQuads {
   int32_t cap = 0, nprogs = 0;
   int64_t blocks = 0;   // of all programs
   float chain[kMaxQuadWaves + 1] = {};  // quad_chains
+  // by waves: row-blocks, and what the launch model charges an item whatever the call (see
+  // choose_quads): microseconds but for staging and stores
+  int32_t n_rb[kMaxQuadWaves + 1] = {};
+  float item_us[kMaxQuadWaves + 1] = {};
   const uint32_t* stream = nullptr;
   const uint32_t* descs = nullptr;
   const QuadProgram* progs = nullptr;
@@ -346,8 +350,13 @@ int quad_waves(const sdnn_plan_s* p, const QuadCfg& cfg);
 // How the kernel reads B and writes C (16- or 4-byte pieces, streamed or through the caches),
 // which their alignment decides.
 int quad_access(const sdnn_plan_s* p, const float* B, const float* C, int32_t N);
-bool quads_serve(const sdnn_plan_s* p, int32_t N);
-QuadCfg quad_shape(const sdnn_plan_s* p, const float* B, const float* C, int32_t N, bool conv, double* us);
+// (overrides: any environment variable of the tests is set, so that calls without one look for
+// them once)
+bool test_overrides();
+bool quads_serve(const sdnn_plan_s* p, int32_t N, bool overrides);
+QuadCfg quad_shape(const sdnn_plan_s* p, const float* B, const float* C, int32_t N, bool conv, bool overrides,
+                   double* us);
+void quad_item_times(DevQuads* d, int32_t K);  // fills n_rb and item_us
 // Whether a workgroup's chain of blocks is far longer than a wave's share of W (32 entries a
 // block): filler, and waves that wait for one another.  Below 1.9 times the panel kernel was never
 // the faster one by more than 5 % in the measurements below on_quads; uniform rows of 2 % and more

@@ -711,6 +711,10 @@ hipError_t launch_reduce(const float* ws, float* C, const float* bias, const int
 // consecutive segments) for a requested count (0: choose_splits).
 int split_runs_of(const sdnn_plan_s* p, int32_t N, int splits, bool conv, int* seg_per_split) {
   const int total_seg = p->pk[0].nseg;
+  if (total_seg == 1) {  // nothing to choose
+    if (seg_per_split) *seg_per_split = 1;
+    return 1;
+  }
   if (splits <= 0 && !conv)  // the count sdnn_plan_tune measured fastest at this N
     for (int i = 0; i < p->ntuned; ++i)
       if (p->tuned[i].N == N && p->tuned[i].splits > 0) splits = p->tuned[i].splits;
@@ -913,14 +917,15 @@ void launch_shape(const sdnn_plan_s* p, int32_t N, int32_t* panel_rows, int32_t*
 // the panel kernel, up to 2.8 times; with this rule 11 do, up to 1.33 times (327 x 5632 in blocks of
 // 8, 2309 x 2112 in scattered windows of 211: the model takes 25 % off the row-quad kernel's time).
 static bool on_quads(const sdnn_plan_s* p, const float* B, const float* C, int32_t N, bool conv, QuadCfg* cfg) {
-  if (!quads_serve(p, N)) return false;
+  const bool overrides = test_overrides();
+  if (!quads_serve(p, N, overrides)) return false;
   for (int i = 0; i < p->ntuned && !conv; ++i)
     if (p->tuned[i].N == N && p->tuned[i].access == quad_access(p, B, C, N)) {
       *cfg = p->tuned[i].quad;
       return p->tuned[i].quads != 0;
     }
   double us = 0.0;
-  *cfg = quad_shape(p, B, C, N, conv, &us);
+  *cfg = quad_shape(p, B, C, N, conv, overrides, &us);
   if (!p->uneven_chains || us == 0.0 || !quads_uneven(p->quads[cfg->pack], quad_waves(p, *cfg), p->nnz)) return true;
   const bool aligned = N % 4 == 0 && (((uintptr_t)B | (uintptr_t)C) & 15) == 0;
   return panel_time(p, N, aligned, conv) >= 1.05 * us;
@@ -1001,9 +1006,10 @@ hipError_t tune_spmm(sdnn_plan_s* p, const float* B, float* C, int32_t N, hipStr
     }
   // the row-quad kernel, where it serves the call: every packing with its most consumer waves
   // and three smaller counts, and the cost model's choice
-  if (err == hipSuccess && quads_serve(p, N)) {
+  const bool overrides = test_overrides();
+  if (err == hipSuccess && quads_serve(p, N, overrides)) {
     double us;
-    std::vector<QuadCfg> quads{quad_shape(p, B, C, N, false, &us)};
+    std::vector<QuadCfg> quads{quad_shape(p, B, C, N, false, overrides, &us)};
     for (int k = 0; k < p->nquads; ++k)
       for (int w : {12, 9, 6, 3})
         if (w <= std::max(3, p->quads[k].nprogs)) quads.push_back(QuadCfg{k, w});

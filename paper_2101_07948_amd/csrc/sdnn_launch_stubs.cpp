@@ -40,6 +40,7 @@ void launch_shape(const sdnn_plan_s* p, int32_t, int32_t* panel_rows, int32_t* w
   *waves = 1;
   *tile_cols = kTileCols;
 }
+void quad_item_times(DevQuads*, int32_t) {}
 void launch_quad_shape(const sdnn_plan_s*, int32_t, int32_t* program_rows, int32_t* waves) {
   *program_rows = *waves = 0;
 }

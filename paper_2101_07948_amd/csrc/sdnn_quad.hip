@@ -31,6 +31,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <stdlib.h>
+#include <string.h>
+#include <unistd.h>
 
 #include <algorithm>
 
@@ -545,27 +547,26 @@ int env_or(const char* name, int dflt) {
 // noise of the single timings included.  Programs of 32 rows, streamed, only from 8 chunks of
 // K up: below, their bursts of stores are what is waited for (1500 x 100 at 90 %, N = 16384: 34.8
 // against 30.8 us with 16-row ones).
+// All of it but staging and stores is the packing's, computed with the plan (quad_item_times): per
+// call the 48 candidates take a division each.
 QuadCfg choose_quads(const sdnn_plan_s* p, int N, QuadStage stage, bool cached, double* us) {
   const int64_t tiles = (N + kQuadTileCols - 1) / kQuadTileCols;
   const uint32_t cus = p->num_cus > 0 ? p->num_cus : 256;
   const int chunks = (p->K + kQuadChunk - 1) / kQuadChunk;
-  const double t_stage = stage == kQuadVec ? 0.13 : stage == kQuadDword ? 0.29 : 0.20;
+  const float t_stage = stage == kQuadVec ? 0.13f : stage == kQuadDword ? 0.29f : 0.20f;
   QuadCfg best{0, 1};
-  double best_t = -1.0;
+  float best_t = -1.0f;
   for (int i = 0; i < p->nquads; ++i) {
     const DevQuads& d = p->quads[i];
     if (d.cap == 8 && chunks < 8 && !cached) continue;
-    const bool wide = d.cap <= 2;
-    const double lat = wide ? 0.080 : 0.112, thr = (wide ? 0.039 : 0.016) * (double)d.blocks / d.nprogs;
-    const double fixed = (wide ? 0.082 : 0.074) * chunks + (wide ? 0.21 : d.cap == 4 ? 0.17 : 0.58);
-    const double store = (d.cap == 8 ? 0.0054 : 0.0071) * (cached ? 1.33 : 1.0) * 4.0 * d.cap;
+    const float store = (d.cap == 8 ? 0.0054f : 0.0071f) * (cached ? 1.33f : 1.0f) * 4.0f * d.cap;
     for (int w = 1; w <= std::min(kMaxQuadWaves, d.nprogs); ++w) {
-      const int64_t items = tiles * ((d.nprogs + w - 1) / w);
-      // (the loop is host time of every call: 32-bit divisions where they do)
+      const int64_t items = tiles * d.n_rb[w];
+      // (32-bit divisions where they do)
       const int64_t rounds = items < (int64_t)1 << 31 ? ((uint32_t)items + cus - 1) / cus : (items + cus - 1) / cus;
       const int staged = rounds > 1 ? (chunks + 3) / 4 * 4 : chunks;
-      const double t = rounds * (lat * d.chain[w] + thr * std::max(0.25 * w, 1.0) + fixed + t_stage * staged + store * w);
-      if (best_t < 0.0 || t < best_t) {
+      const float t = rounds * (d.item_us[w] + t_stage * staged + store * w);
+      if (best_t < 0.0f || t < best_t) {
         best_t = t;
         best = QuadCfg{i, w};
       }
@@ -577,11 +578,29 @@ QuadCfg choose_quads(const sdnn_plan_s* p, int N, QuadStage stage, bool cached, 
 
 }  // namespace
 
+void quad_item_times(DevQuads* d, int32_t K) {
+  const int chunks = (K + kQuadChunk - 1) / kQuadChunk;
+  const bool wide = d->cap <= 2;
+  const double lat = wide ? 0.080 : 0.112, thr = (wide ? 0.039 : 0.016) * (double)d->blocks / std::max(1, d->nprogs);
+  const double fixed = (wide ? 0.082 : 0.074) * chunks + (wide ? 0.21 : d->cap == 4 ? 0.17 : 0.58);
+  for (int w = 1; w <= kMaxQuadWaves; ++w) {
+    d->n_rb[w] = (d->nprogs + w - 1) / w;
+    d->item_us[w] = (float)(lat * d->chain[w] + thr * std::max(0.25 * w, 1.0) + fixed);
+  }
+}
+
+bool test_overrides() {
+  for (char** e = environ; e && *e; ++e)
+    if (strncmp(*e, "SDNN_", 5) == 0) return true;
+  return false;
+}
+
 // Calls under the panel kernel's test overrides run on it.
-bool quads_serve(const sdnn_plan_s* p, int32_t N) {
-  return p->nquads > 0 && p->K > 0 && (uint64_t)N * 4u * 16 < ((uint64_t)1 << 31) &&
-         !getenv("SDNN_FORCE_WAVES") && !getenv("SDNN_FORCE_WG_PER_TILE") &&
-         !getenv("SDNN_FORCE_TILE_MAJOR_WGS");
+bool quads_serve(const sdnn_plan_s* p, int32_t N, bool overrides) {
+  if (overrides && (getenv("SDNN_FORCE_WAVES") || getenv("SDNN_FORCE_WG_PER_TILE") ||
+                    getenv("SDNN_FORCE_TILE_MAJOR_WGS")))
+    return false;
+  return p->nquads > 0 && p->K > 0 && (uint64_t)N * 4u * 16 < ((uint64_t)1 << 31);
 }
 
 static QuadStage quad_stage(const float* B, const float* C, int32_t N) {
@@ -592,8 +611,10 @@ int quad_access(const sdnn_plan_s* p, const float* B, const float* C, int32_t N)
   return 2 * (int)quad_stage(B, C, N) + (cached_stores(p, C, N) ? 1 : 0);
 }
 
-QuadCfg quad_shape(const sdnn_plan_s* p, const float* B, const float* C, int32_t N, bool conv, double* us) {
+QuadCfg quad_shape(const sdnn_plan_s* p, const float* B, const float* C, int32_t N, bool conv, bool overrides,
+                   double* us) {
   QuadCfg c = choose_quads(p, N, conv ? kQuadConv : quad_stage(B, C, N), cached_stores(p, C, N), us);
+  if (!overrides) return c;
   const int cap = env_or("SDNN_FORCE_QUAD_CAP", 0), waves = env_or("SDNN_FORCE_QUAD_WAVES", 0);  // tests
   for (int i = 0; i < p->nquads; ++i)
     if (p->quads[i].cap == cap) c.pack = i;
