@@ -8,6 +8,7 @@
 
 #include <algorithm>
 #include <array>
+#include <memory>
 #include <utility>
 #include <new>
 #include <vector>
@@ -130,7 +131,9 @@ struct Entry {
 // Writes one group (n <= kGroup real entries from e) with its fields.
 void emit_group(std::vector<uint32_t>& out, const Entry* e, int n, bool first, bool last,
                 int32_t* prev_lo, int32_t* prev_hi) {
-  uint32_t w[kGroup], a[kGroup];
+  const size_t at = out.size();
+  out.resize(at + 2 * kGroup);
+  uint32_t *w = out.data() + at, *a = w + kGroup;
   for (int j = 0; j < kGroup; ++j) {
     w[j] = j < n ? e[j].w : 0u;            // zero-weight copies of the first entry
     a[j] = j < n ? e[j].a : e[0].a;
@@ -141,8 +144,6 @@ void emit_group(std::vector<uint32_t>& out, const Entry* e, int n, bool first, b
   a[kHiWord] |= (uint32_t)hi << kHiShift | (uint32_t)sync << kSyncBit | (uint32_t)last << kEndBit;
   *prev_lo = lo;
   *prev_hi = hi;
-  for (int j = 0; j < kGroup; ++j) out.push_back(w[j]);
-  for (int j = 0; j < kGroup; ++j) out.push_back(a[j]);
 }
 }  // namespace
 
@@ -842,17 +843,24 @@ static int64_t quad_bytes(const QuadPacked& Q) {
          align256((int64_t)Q.rows.size() * 4) * 2;
 }
 
-std::vector<uint32_t> narrow_stream(const std::vector<uint32_t>& entries) {
-  std::vector<uint32_t> out(entries);
+static void write_narrow(const std::vector<uint32_t>& entries, uint32_t* out) {
   const size_t groups = entries.size() / (2 * kGroup);
-  for (size_t g = 0; g < groups; ++g)
+  for (size_t g = 0; g < groups; ++g, out += 2 * kGroup) {
+    const uint32_t* in = entries.data() + g * 2 * kGroup;
     for (int j = 0; j < kGroup; ++j) {
-      uint32_t& a = out[g * 2 * kGroup + kGroup + j];
+      out[j] = in[j];
+      const uint32_t a = in[kGroup + j];
       const uint32_t ring = (a >> kRingRowShift) & (uint32_t)(kRing * kChunk - 1);
       const uint32_t end = (a >> kEndBit) & 1u;
       const uint32_t high = a & ~((1u << kSyncBit) - 1u);  // chunk and sync fields
-      a = high | ring << kRingRowShiftNarrow | end << kEndBitNarrow | (a & ((1u << kRowBits) - 1u));
+      out[kGroup + j] = high | ring << kRingRowShiftNarrow | end << kEndBitNarrow | (a & ((1u << kRowBits) - 1u));
     }
+  }
+}
+
+std::vector<uint32_t> narrow_stream(const std::vector<uint32_t>& entries) {
+  std::vector<uint32_t> out(entries.size());
+  write_narrow(entries, out.data());
   return out;
 }
 
@@ -1005,7 +1013,8 @@ sdnn_status sdnn_plan_create(const int32_t* row_ptr, const int32_t* col_idx, con
         delete plan;
         return SDNN_ERR_ALLOC;
       }
-      std::vector<char> host((size_t)total, 0);
+      // (left as it comes between the arrays: filling it first took as long as packing)
+      const std::unique_ptr<char[]> host(new char[(size_t)total]);
       int64_t off = 0;
       for (size_t i = 0; i < packs.size(); ++i) {
         const Packed& P = packs[i];
@@ -1030,12 +1039,9 @@ sdnn_status sdnn_plan_create(const int32_t* row_ptr, const int32_t* col_idx, con
         d.seg_start = P.seg_start.empty() ? nullptr
                                           : (const int32_t*)(base + b_ent + b_seg + b_rows + b_pos);
         // panel tables in workgroup (slot) order: slot j is panel panel_order[j]
-        char* h = host.data() + off;
+        char* h = host.get() + off;
         if (!P.entries.empty()) memcpy(h, P.entries.data(), P.entries.size() * 4);
-        if (narrow && !P.entries.empty()) {
-          const std::vector<uint32_t> nst = narrow_stream(P.entries);
-          memcpy(h + b_all, nst.data(), nst.size() * 4);
-        }
+        if (narrow) write_narrow(P.entries, (uint32_t*)(h + b_all));
         int32_t* hs = (int32_t*)(h + b_ent);
         int32_t* hr = (int32_t*)(h + b_ent + b_seg);
         int32_t* hp = (int32_t*)(h + b_ent + b_seg + b_rows);
@@ -1051,7 +1057,7 @@ sdnn_status sdnn_plan_create(const int32_t* row_ptr, const int32_t* col_idx, con
         off += packing_bytes(P, narrow);
       }
       if (o.split_chunks > 0 && M > 0) {
-        memcpy(host.data() + perm_off, P0.perm.data(), (size_t)M * 4);
+        memcpy(host.get() + perm_off, P0.perm.data(), (size_t)M * 4);
         plan->d_perm = (const int32_t*)((char*)plan->d_mem + perm_off);
       }
       int64_t qoff = quad_off;
@@ -1061,7 +1067,7 @@ sdnn_status sdnn_plan_create(const int32_t* row_ptr, const int32_t* col_idx, con
         auto put = [&](const auto& v) {
           const void* at = (const char*)plan->d_mem + qoff;
           const size_t bytes = v.size() * sizeof(v[0]);
-          if (bytes) memcpy(host.data() + qoff, v.data(), bytes);
+          if (bytes) memcpy(host.get() + qoff, v.data(), bytes);
           qoff += align256((int64_t)bytes);
           return at;
         };
@@ -1083,7 +1089,7 @@ sdnn_status sdnn_plan_create(const int32_t* row_ptr, const int32_t* col_idx, con
         plan->pk[i].groups = packs[i].stored / kGroup;
         panel_chains(packs[i], plan->pk[i].chain);
       }
-      if (hipMemcpy(plan->d_mem, host.data(), (size_t)total, hipMemcpyHostToDevice) !=
+      if (hipMemcpy(plan->d_mem, host.get(), (size_t)total, hipMemcpyHostToDevice) !=
           hipSuccess) {
         (void)hipGetLastError();
         (void)hipFree(plan->d_mem);

@@ -39,14 +39,21 @@ bool pack_quads(const int32_t* row_ptr, const int32_t* col_idx, const float* val
     while (NS > 1 && (double)NS * (row_ptr[order[i0] + 1] - row_ptr[order[i0]]) > longest) NS /= 2;
     const int RW = 4 * NS, steps = kQuadUnits / NS, to_addr = quad_addr_at(NS);
     int dword[4 * kQuadMaxCap], next_step = NS <= 2 ? NS : NS / 2;  // row j's weight: step 0, and on
-    for (int j = 0; j < RW; ++j) dword[j] = quad_dword(NS, j, 0);
-    int32_t at[4 * kQuadMaxCap], end[4 * kQuadMaxCap];  // next entry and end of each row
+    uint32_t filler[64] = {};  // a block without entries
+    for (int j = 0; j < RW; ++j) {
+      dword[j] = quad_dword(NS, j, 0);
+      for (int st = 0; st < steps; ++st) filler[quad_dword(NS, j, st) + to_addr] = kQuadZeroRow;
+    }
+    // next entry, end and column of the next entry (past all columns: none left) of each row
+    int32_t at[4 * kQuadMaxCap], end[4 * kQuadMaxCap], col[4 * kQuadMaxCap];
     bool any = false;
     for (int j = 0; j < RW; ++j) {
       at[j] = end[j] = 0;
-      if (i0 + j >= M) continue;
-      at[j] = row_ptr[order[i0 + j]];
-      end[j] = row_ptr[order[i0 + j] + 1];
+      if (i0 + j < M) {
+        at[j] = row_ptr[order[i0 + j]];
+        end[j] = row_ptr[order[i0 + j] + 1];
+      }
+      col[j] = at[j] < end[j] ? col_idx[at[j]] : INT32_MAX;
       any |= at[j] < end[j];
     }
     QuadProgram P{-1, (int32_t)Q.descs.size(), NS, 0};
@@ -64,36 +71,29 @@ bool pack_quads(const int32_t* row_ptr, const int32_t* col_idx, const float* val
       };
       for (;;) {
         int32_t low = INT32_MAX;  // the program's lowest unread column
-        for (int j = 0; j < RW; ++j)
-          if (at[j] < end[j]) low = std::min(low, col_idx[at[j]]);
+        for (int j = 0; j < RW; ++j) low = std::min(low, col[j]);
         if (low == INT32_MAX) break;
         const int32_t clo = low / kQuadChunk;
-        const int64_t limit = ((int64_t)clo + window) * kQuadChunk;  // first column not taken
+        const int32_t limit = (clo + window) * kQuadChunk;  // first column not taken
         int32_t high = low;
         const size_t base = Q.stream.size();
         if ((int64_t)base * 4 >= max_bytes) {
           Q = QuadPacked();
           return false;
         }
-        Q.stream.resize(base + 64);
+        Q.stream.insert(Q.stream.end(), filler, filler + 64);
         uint32_t* blk = Q.stream.data() + base;
         for (int j = 0; j < RW; ++j) {
           uint32_t* to = blk + dword[j];
-          int32_t e = at[j];
-          const int32_t stop = end[j];
-          for (int st = 0; st < steps; ++st, to += next_step) {
-            uint32_t w = 0, addr = kQuadZeroRow;
-            if (e < stop && col_idx[e] < limit) {
-              const int32_t k = col_idx[e];
-              memcpy(&w, &values[e], 4);
-              addr = quad_address(k);
-              high = std::max(high, k);
-              ++e;
-            }
-            to[0] = w;
-            to[to_addr] = addr;
+          int32_t e = at[j], k = col[j];
+          for (int st = 0; st < steps && k < limit; ++st, to += next_step) {
+            memcpy(to, &values[e], 4);
+            to[to_addr] = quad_address(k);
+            high = std::max(high, k);
+            k = ++e < end[j] ? col_idx[e] : INT32_MAX;
           }
           at[j] = e;
+          col[j] = k;
         }
         const int32_t chi = high / kQuadChunk;
         if (n > 0 && (clo != lo || chi > hi || n == kQuadMaxBlocks)) close();
