@@ -16,26 +16,27 @@ namespace {
 //     GELU(x) = max(x, 0) - 0.5 |x| erfc(z)
 // for either sign (no cancellation: the second term is at most half the first, or alone).
 // Evaluated on y = |x| sqrt(0.5 log2 e), so that e^(-z^2) = 2^(-y^2), with the factor 0.5 |x| / y
-// folded into the coefficients; their last bits (and p's) were then searched for the smallest
-// error in float arithmetic, because the rounded ones no longer sum to erfc(0) = 1.  The
-// reciprocal and the exponential are the hardware's (v_rcp_f32, v_exp_f32, about 1 ulp).  The
-// result is within 0.5 |x| * 6e-7 of the exact GELU, far inside the 1e-6 floor of the parity bar
-// at the |x| these layers reach; against the coefficients as printed, over |x| distributed
-// N(0, 0.005^2) to N(0, 5^2), the 2-norm error is 0.92-1.006 of theirs.  12 plain instructions
-// and the two special ones, where the two-sided form took 18: on the 3072 x 768 layer at
-// N = 16384 the GELU of 50 M outputs is a third of the vector instructions (107.7 -> 103.1 us).
+// folded into the coefficients; their last bits (and p's) were then searched on the GPU for the
+// smallest error, because the rounded ones no longer sum to erfc(0) = 1.  The reciprocal and the
+// exponential are the hardware's (v_rcp_f32, v_exp_f32, about 1 ulp).  Over every float of 1e-7 <=
+// |x| <= 14 the result is within 0.5 |x| * 6.31e-7 of the exact GELU (6.43e-7 with the coefficients
+// as printed, in the two-sided form), far inside the 1e-6 floor of the parity bar at the |x| these
+// layers reach; over x distributed N(0, 0.01^2) to N(0, 5^2) the 2-norm of the error is 0.93-1.007
+// of theirs, 1.05 at N(0, 0.003^2).  12 plain instructions and the two special ones, where the
+// two-sided form took 18: on the 3072 x 768 layer at N = 16384 the GELU of 50 M outputs is a third
+// of the vector instructions (107.7 -> 103.1 us).
 __device__ __forceinline__ float gelu(float x) {
-  const float y = fabsf(x) * 0.8493217825889587f;
+  // (an infinite x: its factor stays finite at +inf, whose q is 0, and gives NaN at -inf)
+  const float y = fabsf(__builtin_elementwise_minimum(x, 3.0e38f)) * 0.849321783f;
   const float e = __builtin_amdgcn_exp2f(-(y * y));
-  const float t = __builtin_amdgcn_rcpf(fmaf(y, 0.27273744344711304f, 1.0f));
-  float q = fmaf(t, 0.6248548030853271f, -0.855477511882782f);
-  q = fmaf(t, q, 0.8367929458618164f);
-  q = fmaf(t, q, -0.16748465597629547f);
-  q = fmaf(t, q, 0.15001946687698364f);
+  const float t = __builtin_amdgcn_rcpf(fmaf(y, 0.272737592f, 1.0f));
+  float q = fmaf(t, 0.624854565f, -0.855477035f);
+  q = fmaf(t, q, 0.836792111f);
+  q = fmaf(t, q, -0.167484373f);
+  q = fmaf(t, q, 0.15001978f);
   q *= t;
   q *= e;
-  // (an infinite x has q = 0: its factor stays finite)
-  return fmaf(-fminf(y, 3.402823466e38f), q, fmaxf(x, 0.0f));
+  return fmaf(-y, q, fmaxf(x, 0.0f));
 }
 
 // C is written once and not read again by the kernel: its stores are non-temporal, so the
