@@ -55,8 +55,10 @@ def check_conv(L, label="", **plan_kw):
     (40, 16, 7, 7, 12, 0.9, "gelu"),     # 7 x 7 images, N = 588 (ragged last tile)
 ])
 def test_conv_parity(OC, IC, H, W, NB, sparsity, epi):
+    """On the default plan's kernel and on the panel kernel's own choice of packing."""
     L = inputs.conv_layer(OC, IC, H, W, NB, sparsity, layer=OC + IC + H, epi=epi)
-    check_conv(L, f"OC={OC} IC={IC} {H}x{W}x{NB} s={sparsity} {epi}")
+    label = f"OC={OC} IC={IC} {H}x{W}x{NB} s={sparsity} {epi}"
+    assert np.array_equal(check_conv(L, label), check_conv(L, label, grouping="balanced"))
 
 
 def test_conv_tall_panels_and_out_permuted():

@@ -228,21 +228,24 @@ def test_row_permutation_equivariance_bitexact():
 def test_tall_panels_at_large_N():
     """768 rows over 32 column tiles: 4-row panels need two rounds of workgroups on 256
     CUs, 8- and 12-row ones one, and 8-row panels already hold 25.6 entries per chunk at
-    10 %, so the default plan runs its 8-row packing (as sdnn_plan_launch_shape reports):
-    checked against the oracle, and bit-identical to a 4-row-only plan (every row sums its
-    entries in ascending column order either way)."""
+    10 %, so the panel kernel runs its 8-row packing (as sdnn_plan_launch_shape reports; a
+    plan that fixes the grouping runs on it): bit-identical to a 4-row-only plan and to the
+    default plan (every row sums its entries in ascending column order either way), which is
+    checked against the oracle."""
     M, K, N = 768, 1024, 8192
     W = inputs.pattern_uniform(M, K, 0.1, inputs.CFG_TEST, 21, 0.05)
     B = inputs.dense_B(K, N, inputs.CFG_TEST, 21)
     bias = inputs.bias_normal(M, inputs.CFG_TEST, 21, 0.02)
-    with sd.Plan.from_csr(W) as plan:
+    with sd.Plan.from_csr(W, grouping="balanced") as plan:
+        assert plan.launch_quads(N) is None
         if torch.cuda.get_device_properties(0).multi_processor_count == 256:
             assert plan.launch_shape(N)["panel_rows"] == 8
+        tall = gpu_spmm(plan, B, bias, "relu")
     got = check(W.row_ptr, W.col_idx, W.values, M, K, B, bias, "relu", label="tall")
     with sd.Plan.from_csr(W, panel_rows=4) as p4:
         assert p4.info["tall_panel_rows"] == 0
         short = gpu_spmm(p4, B, bias, "relu")
-    assert np.array_equal(got, short)
+    assert np.array_equal(got, short) and np.array_equal(tall, short)
 
 
 def test_out_permuted_writes_rows_in_plan_order():
@@ -314,17 +317,23 @@ def test_balanced_order():
         assert np.all(np.abs(got - ref) <= tolerance(bound, ref, L.epi))
 
 
-def test_plan_tune():
+@pytest.mark.parametrize("grouping", ["auto", "balanced"])
+def test_plan_tune(grouping):
     """sdnn_plan_tune times the plan's launch shapes at one N and records the fastest;
-    later calls at that N use it and give bit-identical results (each row still sums in
+    later calls at that N use it (the panel shape on a plan of the panel kernel, the faster
+    of both kernels on a default one) and give bit-identical results (each row still sums in
     ascending column order), other N keep the heuristic."""
     w = inputs.workload("c2")
     L = w.layers[0]
-    with sd.Plan.from_csr(L.W) as plan:
+    with sd.Plan.from_csr(L.W, grouping=grouping) as plan:
+        other_rule = plan.launch_quads(300), plan.launch_shape(300)
         before = gpu_spmm(plan, w.B, L.bias, L.epi)
         shape = plan.tune(w.N)
         assert shape["panel_rows"] in (4, 8, 12) and 1 <= shape["waves"] <= 12
         assert plan.launch_shape(w.N) == shape
+        assert (plan.launch_quads(300), plan.launch_shape(300)) == other_rule
+        if grouping == "balanced":
+            assert plan.launch_quads(w.N) is None
         after = gpu_spmm(plan, w.B, L.bias, L.epi)
         assert np.array_equal(before, after)
         B2 = inputs.dense_B(L.W.K, 300, inputs.CFG_TEST, 61)
@@ -462,8 +471,8 @@ def test_dense_comparison_kernel(M, K, N):
 
 
 def test_launch_shape_follows_density_and_grid():
-    """The default plan's packing and tile width per call (sdnn_plan_launch_shape) on 256
-    CUs: 4-row panels when they fill the device at 10 % (W0 at N = 4096), 8-row ones when
+    """The panel kernel's packing and tile width per call (sdnn_plan_launch_shape; the plans
+    fix the grouping, so their calls run on it) on 256 CUs: 4-row panels when they fill the device at 10 % (W0 at N = 4096), 8-row ones when
     4-row panels need more rounds (W0 at N = 16384), 12-row ones at 97 % where shorter panels
     hold too few entries per chunk (C5's 768-row layer at N = 8192), 16-row ones where they
     need the fewest rounds of workgroups (M = K = 2048 at 95 %), all on 256-column tiles;
@@ -480,8 +489,9 @@ def test_launch_shape_follows_density_and_grid():
                              (c5[0].W, 16384, 32, 128), (c5[4].W, 16384, 32, 128),
                              (inputs.s_layer(2048, 2048, 0.95).W, 4096, 16, 256),
                              (w0, 1024, 4, 128), (c2, 1024, 4, 128), (c5[5].W, 1024, 8, 128)):
-        with sd.Plan.from_csr(W) as plan:
+        with sd.Plan.from_csr(W, grouping="balanced") as plan:
             got = plan.launch_shape(N)
+            assert plan.launch_quads(N) is None
         assert (got["panel_rows"], got["tile_cols"]) == (want, tile), (W.M, W.K, N, got)
         assert 1 <= got["waves"] <= 12
     with sd.Plan.from_csr(w0, panel_rows=16) as plan:

@@ -225,14 +225,15 @@ def test_poll_budget(budget):
 
 
 def test_tune_searches_both_widths():
-    """sdnn_plan_tune times both tile widths; whichever it records, later calls use it and
-    agree with the oracle."""
+    """sdnn_plan_tune times both tile widths; whichever it records, later calls use it (on a
+    plan of the panel kernel) and agree with the oracle."""
     W = inputs.pattern_uniform(768, 768, 0.1, inputs.CFG_TEST, 5100, 0.02)
     N = 1024
     B = inputs.dense_B(768, N, inputs.CFG_TEST, 5101)
-    with sd.Plan.from_csr(W) as plan:
+    with sd.Plan.from_csr(W, grouping="balanced") as plan:
         Bt = torch.from_numpy(B).to(DEV)
         shape = plan.tune(N, Bt, torch.empty(768, N, device=DEV))
+        assert plan.launch_quads(N) is None
         assert shape["tile_cols"] in (128, 256)
         assert plan.launch_shape(N) == shape
         got = run(plan, B, None, "none", Bt=Bt)
@@ -293,20 +294,21 @@ def test_deep_panels_need_128_column_calls():
         assert plan.launch_shape(130) == before
 
 
-def test_default_plan_takes_deep_panels_at_97_percent():
-    """C5's 97 % layers at N = 16384 run on the default plan's 32-row packing with 12
-    consumer waves on 128-column tiles; at N = 8192 the 768-row layers' deep grid would
+def test_panel_kernel_takes_deep_panels_at_97_percent():
+    """C5's 97 % layers at N = 16384 run on the 32-row packing with 12 consumer waves on
+    128-column tiles of the panel kernel (of plans that fix the grouping); at N = 8192 the 768-row layers' deep grid would
     not fill the CUs and they keep the other packings."""
     if torch.cuda.get_device_properties(0).multi_processor_count != 256:
         pytest.skip("the expected shapes are those of a 256-CU device")
     c5 = inputs.workload("c5", N=4, num_layers=1).layers
     for li in (0, 4, 5):
-        with sd.Plan.from_csr(c5[li].W) as plan:
+        with sd.Plan.from_csr(c5[li].W, grouping="balanced") as plan:
+            assert plan.launch_quads(16384) is None
             assert plan.launch_shape(16384) == {"panel_rows": 32, "waves": 12, "tile_cols": 128}
             if c5[li].W.M == 768:
                 assert plan.launch_shape(8192)["panel_rows"] != 32
     w0 = inputs.workload("w0", N=4).layers[0].W
-    with sd.Plan.from_csr(w0) as plan:  # 90 %: too dense for them
+    with sd.Plan.from_csr(w0, grouping="balanced") as plan:  # 90 %: too dense for them
         assert plan.launch_shape(16384)["panel_rows"] != 32
 
 
@@ -340,7 +342,7 @@ def test_tuned_deep_shape_with_a_call_that_cannot_use_it():
     L = inputs.workload("c5", N=4, num_layers=1).layers[5]
     W, N = L.W, 16384
     B = inputs.dense_B(W.K, N, inputs.CFG_TEST, 5800)
-    with sd.Plan.from_csr(W) as plan:
+    with sd.Plan.from_csr(W, grouping="balanced") as plan:  # (the panel kernel's)
         Bt = torch.from_numpy(B).to(DEV)
         plan.tune(N, Bt, torch.empty(W.M, N, device=DEV))
         flat = torch.empty(W.K * N + 1, device=DEV)
