@@ -20,15 +20,14 @@
 //   * Each row sums its entries in ascending column order with fused multiply-adds, as in
 //     every kernel of the library, so C is the same bit for bit.
 //
-// What bounds it: no unit alone.  A quad-step (four entries x 64 columns) reads 1 KB of B, 4.05
-// cycles of a CU's LDS, and its FMAs, address and weight ops take 16.4 cycles of a SIMD (a quarter
-// of the CU) in groups of 4 lanes and 22.7 in groups of 16, so the groups of 4 are taken where a
-// workgroup has rows enough to fill its waves with them.  On the 768 x 3072 layer at 90 %, N = 4096
-// (97 k cycles) the steps are 66 % of the SIMDs' time and their reads 65 % of LDS's, fillers
-// included, with no bank conflicts; waves wait 31 % of theirs, and each CU has one item, whose start
-// and drain nothing overlaps.  Smaller calls wait more (768 x 768, N = 1024: 54 %).  Measured against
-// the panel kernel: that layer 66.5 -> 46.8-48.8 us, 768 x 768 at 90 %, N = 1024 13.6 -> 8.3 us, 2048 x
-// 2048 at 70 %, N = 512 55.9 -> 36.1 us, 3072 x 768 at 97 %, N = 16384 with GELU 124.1 -> 100.1 us.
+// What bounds it: LDS.  Every entry reads 16 bytes of B per four columns, 1 KB per quad-step
+// (four entries x 64 columns), 4.05 cycles of a CU's LDS; the FMAs, address and weight ops of a
+// quad-step take 16.4 cycles of a SIMD (a quarter of the CU) in groups of 4 lanes and 22.7 in
+// groups of 16, so the groups of 4 run at LDS's pace (the 768 x 3072 layer at 90 %, N = 4096:
+// LDS active in 76 % of the kernel's cycles, no bank conflicts) and are taken where a workgroup
+// has rows enough to fill its waves with them.  Measured against the panel kernel: that layer
+// 66.4 -> 47.3 us, 768 x 768 at 90 %, N = 1024 13.6 -> 8.4 us, 2048 x 2048 at 70 %, N = 512
+// 56.0 -> 36.2 us, 3072 x 768 at 97 %, N = 16384 with GELU 124.2 -> 108.6 us.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <stdlib.h>
@@ -300,83 +299,48 @@ __device__ __forceinline__ void store_vec(float* c, float x, float y, float z, f
 // (a 16-byte store needs 4-byte alignment only)
 typedef nt_float4 __attribute__((aligned(4))) dword_float4;
 
-__device__ __forceinline__ float half_mirror(float x) {  // of lane 7 - l of the lane's eight
-  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x141, 0xf, 0xf, true));
-}
-
-// Four columns from n on of a row of C.
-template <int STAGE, bool CACHED>
-__device__ __forceinline__ void store_four(float* c, int n, int N, const float (&e)[4]) {
-  if constexpr (STAGE == kQuadDword) {
-    if (n + 4 <= N) {
-      store_vec<dword_float4, CACHED>(c + n, e[0], e[1], e[2], e[3]);
-    } else {
-#pragma unroll
-      for (int k = 0; k < 3; ++k)
-        if (n + k < N) c[n + k] = e[k];
-    }
-  } else if (n < N) {
-    store_vec<nt_float4, CACHED>(c + n, e[0], e[1], e[2], e[3]);
-  }
-}
-
-// PAIRED (groups of 4 lanes): a group holds 16 columns of its row in each of four vectors, 64 bytes a
-// store.  Two neighbouring groups exchange every second vector, and both write 128 bytes, an L2
-// line, of one group's row and then of the other's.  (Vector 2 p + 1 of a group of the pair is the
-// quarter beside the other's vector 2 p, since quarters are i ^ (g % 4); half_mirror swaps the groups
-// and turns their lanes round.)  See paired_stores.
-template <int NS, int STAGE, bool PAIRED, int EPI, bool CACHED, int SETS, int ACCS>
+template <int NS, int STAGE, int EPI, bool CACHED, int SETS, int ACCS>
 __device__ __forceinline__ void store_program(const group_acc_t<ACCS> (&acc)[SETS], const int (&out)[SETS],
                                               const float (&bb)[SETS], float* C, int n0, int lane, int N) {
   constexpr int kGroup = NS <= 2 ? 16 : 4, kVecs = ACCS / 4;
-  const int group4 = lane / kGroup % 4;
+  const int quarter = lane / kGroup % 4;
 #pragma unroll
   for (int q = 0; q < SETS; ++q) {
     float v[ACCS];
 #pragma unroll
     for (int k = 0; k < ACCS; ++k) v[k] = activation(acc[q][k] + bb[q], EPI);
-    if constexpr (!PAIRED || kGroup == 16) {
-      if (out[q] < 0) continue;
-      float* c = C + (size_t)out[q] * N;
+    if (out[q] < 0) continue;
+    float* c = C + (size_t)out[q] * N;
 #pragma unroll
-      for (int i = 0; i < kVecs; ++i) {
-        const float e[4] = {v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]};
-        store_four<STAGE, CACHED>(c, n0 + 4 * (lane % kGroup) + 4 * kGroup * (kVecs > 1 ? i ^ group4 : 0), N, e);
-      }
-    } else {
-      const bool odd = lane & 4;
-      const int other = __builtin_amdgcn_mov_dpp(out[q], 0x141, 0xf, 0xf, true);
-      const int row0 = odd ? other : out[q], row1 = odd ? out[q] : other;
-      const int slot = lane & 3;
+    for (int i = 0; i < kVecs; ++i) {
+      const int n = n0 + 4 * (lane % kGroup) + 4 * kGroup * (kVecs > 1 ? i ^ quarter : 0);
+      const float *e = v + 4 * i;
+      if constexpr (STAGE == kQuadDword) {
+        if (n + 4 <= N) {
+          store_vec<dword_float4, CACHED>(c + n, e[0], e[1], e[2], e[3]);
+        } else {
 #pragma unroll
-      for (int p = 0; p < 2; ++p) {
-        float e0[4], e1[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const float mine = v[8 * p + k], theirs = half_mirror(v[8 * p + 4 + k]);
-          e0[k] = odd ? theirs : mine;
-          e1[k] = odd ? mine : theirs;
+          for (int k = 0; k < 3; ++k)
+            if (n + k < N) c[n + k] = e[k];
         }
-        const int quarter = (2 * p ^ (group4 & 2)) + (odd ? 1 : 0);
-        const int n = n0 + 16 * quarter;
-        if (row0 >= 0) store_four<STAGE, CACHED>(C + (size_t)row0 * N, n + 4 * (odd ? 3 - slot : slot), N, e0);
-        if (row1 >= 0) store_four<STAGE, CACHED>(C + (size_t)row1 * N, n + 4 * (odd ? slot : 3 - slot), N, e1);
+      } else if (n < N) {
+        store_vec<nt_float4, CACHED>(c + n, e[0], e[1], e[2], e[3]);
       }
     }
   }
 }
 
-template <int NS, int STAGE, bool PAIRED, bool CACHED, int SETS, int ACCS>
+template <int NS, int STAGE, bool CACHED, int SETS, int ACCS>
 __device__ __forceinline__ void finish_program(const group_acc_t<ACCS> (&acc)[SETS], const int (&out)[SETS],
                                                const float (&bb)[SETS], float* C, int n0, int lane,
                                                const QuadArgs& a) {
   const int epi = epilogue_of(acc[0][0], a.epi);
   if (epi == SDNN_EPI_GELU)
-    store_program<NS, STAGE, PAIRED, SDNN_EPI_GELU, CACHED>(acc, out, bb, C, n0, lane, a.N);
+    store_program<NS, STAGE, SDNN_EPI_GELU, CACHED>(acc, out, bb, C, n0, lane, a.N);
   else if (epi == SDNN_EPI_RELU)
-    store_program<NS, STAGE, PAIRED, SDNN_EPI_RELU, CACHED>(acc, out, bb, C, n0, lane, a.N);
+    store_program<NS, STAGE, SDNN_EPI_RELU, CACHED>(acc, out, bb, C, n0, lane, a.N);
   else
-    store_program<NS, STAGE, PAIRED, SDNN_EPI_NONE, CACHED>(acc, out, bb, C, n0, lane, a.N);
+    store_program<NS, STAGE, SDNN_EPI_NONE, CACHED>(acc, out, bb, C, n0, lane, a.N);
 }
 
 // A wave's place in its workgroup's items.
@@ -397,7 +361,7 @@ struct QuadCursor {
 // divide the workgroups, all of the wave's): its loop and the epilogue of its rows per item.
 // The rows' tables are read once; read per item, their two dependent loads stood between the
 // items of every wave.
-template <int CAP, int NS, int STAGE, bool PAIRED>
+template <int CAP, int NS, int STAGE>
 __device__ __forceinline__ void run_program(QuadConsumer& ca, bool entries, const int32_t* rows,
                                             const int32_t* outs, float* C, const float* bias,
                                             QuadCursor& cur, int lane, const QuadArgs& a) {
@@ -436,9 +400,9 @@ __device__ __forceinline__ void run_program(QuadConsumer& ca, bool entries, cons
     }
     const int n0 = cur.tile * kQuadTileCols;
     if (a.cached)
-      finish_program<NS, STAGE, PAIRED, true>(acc, out, bb, C, n0, lane, a);
+      finish_program<NS, STAGE, true>(acc, out, bb, C, n0, lane, a);
     else
-      finish_program<NS, STAGE, PAIRED, false>(acc, out, bb, C, n0, lane, a);
+      finish_program<NS, STAGE, false>(acc, out, bb, C, n0, lane, a);
     if (!cur.next(a)) return;
     cur.find(a);
   } while (cur.prog == prog);
@@ -452,7 +416,7 @@ __device__ __forceinline__ void run_program(QuadConsumer& ca, bool entries, cons
 // stratum of the list sorted by length, in snake order over the row-blocks, so that
 // row-blocks carry equal work, and the strata go to the SIMDs (wave w runs on SIMD w % 4)
 // in snake order too.
-template <int CAP, int STAGE, bool PAIRED>
+template <int CAP, int STAGE>
 __global__ __launch_bounds__(1024) void spmm_quad_kernel(
     const uint32_t* __restrict__ stream, const uint32_t* __restrict__ descs,
     const QuadProgram* __restrict__ progs, const int32_t* __restrict__ rows,
@@ -520,29 +484,25 @@ __global__ __launch_bounds__(1024) void spmm_quad_kernel(
     ca.poll_budget = budget;
     const int32_t* r = rows + (size_t)cur.prog * (4 * CAP);
     const int32_t* o = outs + (size_t)cur.prog * (4 * CAP);
-    if (CAP == 8 && P.NS == 8) run_program<CAP, 8, STAGE, PAIRED>(ca, P.start >= 0, r, o, C, bias, cur, lane, a);
-    else if (CAP >= 4 && P.NS == 4) run_program<CAP, 4, STAGE, PAIRED>(ca, P.start >= 0, r, o, C, bias, cur, lane, a);
-    else if (CAP >= 2 && P.NS == 2) run_program<CAP, 2, STAGE, PAIRED>(ca, P.start >= 0, r, o, C, bias, cur, lane, a);
-    else run_program<CAP, 1, STAGE, PAIRED>(ca, P.start >= 0, r, o, C, bias, cur, lane, a);
+    if (CAP == 8 && P.NS == 8) run_program<CAP, 8, STAGE>(ca, P.start >= 0, r, o, C, bias, cur, lane, a);
+    else if (CAP >= 4 && P.NS == 4) run_program<CAP, 4, STAGE>(ca, P.start >= 0, r, o, C, bias, cur, lane, a);
+    else if (CAP >= 2 && P.NS == 2) run_program<CAP, 2, STAGE>(ca, P.start >= 0, r, o, C, bias, cur, lane, a);
+    else run_program<CAP, 1, STAGE>(ca, P.start >= 0, r, o, C, bias, cur, lane, a);
     budget = ca.poll_budget;
   }
 }
 
-template <int CAP, int STAGE, bool PAIRED = false>
+template <int CAP, int STAGE>
 hipError_t launch_cap(const DevQuads& d, const float* B, float* C, const float* bias,
                       const QuadArgs& args, int waves, int grid, hipStream_t stream) {
-  hipLaunchKernelGGL((spmm_quad_kernel<CAP, STAGE, PAIRED>), dim3(grid), dim3(64 * (waves + kQuadProducers)),
+  hipLaunchKernelGGL((spmm_quad_kernel<CAP, STAGE>), dim3(grid), dim3(64 * (waves + kQuadProducers)),
                      0, stream, d.stream, d.descs, d.progs, d.rows, d.outs, B, C, bias, args);
   return hipGetLastError();
 }
 
 template <int STAGE>
 hipError_t launch_stage(const DevQuads& d, const float* B, float* C, const float* bias,
-                        const QuadArgs& args, int waves, int grid, bool paired, hipStream_t stream) {
-  if constexpr (STAGE == kQuadVec) {
-    if (paired && d.cap == 4) return launch_cap<4, STAGE, true>(d, B, C, bias, args, waves, grid, stream);
-    if (paired && d.cap == 8) return launch_cap<8, STAGE, true>(d, B, C, bias, args, waves, grid, stream);
-  }
+                        const QuadArgs& args, int waves, int grid, hipStream_t stream) {
   switch (d.cap) {
     case 1: return launch_cap<1, STAGE>(d, B, C, bias, args, waves, grid, stream);
     case 2: return launch_cap<2, STAGE>(d, B, C, bias, args, waves, grid, stream);
@@ -566,14 +526,6 @@ bool cached_stores(const sdnn_plan_s* p, const float* C, int32_t N) {
   if (N % 16 != 0 || ((uintptr_t)C & 63) != 0) return bytes >= (int64_t)8 << 20;
   return p->K <= 32 && bytes >= (int64_t)48 << 20;
 }
-
-// Whether programs of 16 and 32 rows stream C in paired stores (store_program).  Where C comes to more
-// than the memory-side cache (256 MB) takes beside B, its 64-byte pieces reach memory as half lines
-// each time another buffer takes its place: with buffers of over 1 GiB in turn the 3072 x 768 layer
-// at 97 %, N = 16384 (201 MB of C) took 151 us, 125 paired (123 on the panel kernel), 3072 x 1536 at 98 %
-// 189 and 174; with one buffer 103 and 100, 146 and 145.  Smaller ones lose to the exchange what they
-// gain (94 %, N = 4096, 50 MB: 44.1 and 46.2 us with one buffer).
-bool paired_stores(const sdnn_plan_s* p, int32_t N) { return (int64_t)p->M * N * 4 >= (int64_t)128 << 20; }
 
 int env_or(const char* name, int dflt) {
   const char* s = getenv(name);
@@ -701,11 +653,10 @@ hipError_t launch_quads(const sdnn_plan_s* p, const float* B, float* C, int32_t 
   args.W = conv_hwn ? conv_hwn[1] : 0;
   args.NB = conv_hwn ? conv_hwn[2] : 0;
   const int grid = args.per_xcd * 8;
-  const bool paired = !args.cached && paired_stores(p, N);
-  if (conv_hwn) return launch_stage<kQuadConv>(d, B, C, bias, args, waves, grid, false, stream);
+  if (conv_hwn) return launch_stage<kQuadConv>(d, B, C, bias, args, waves, grid, stream);
   return quad_stage(B, C, N) == kQuadVec
-             ? launch_stage<kQuadVec>(d, B, C, bias, args, waves, grid, paired, stream)
-             : launch_stage<kQuadDword>(d, B, C, bias, args, waves, grid, false, stream);
+             ? launch_stage<kQuadVec>(d, B, C, bias, args, waves, grid, stream)
+             : launch_stage<kQuadDword>(d, B, C, bias, args, waves, grid, stream);
 }
 
 }  // namespace sdnn

@@ -273,12 +273,10 @@ def test_budget_is_the_waves_in_total(force, kw, M, tile):
     (700, 40, 3092, 0.2), (700, 40, 3001, 0.2),   # rows of C off 64 bytes, past 8 MB
     (160, 70, 1003, 0.3),                         # the same, below it
     (800, 32, 16384, 0.2), (800, 33, 16384, 0.2),  # aligned rows past 48 MB, K of 32 and above
-    (2047, 70, 16400, 0.1), (2045, 70, 16400, 0.1),  # past 128 MiB: paired stores, rows past M, a
-                                                     # last tile of 16 columns; and just below
 ])
 def test_output_stores(force, cap, M, K, N, density):
-    """Both sides of the rules that store C through the caches or stream it, and stream it in
-    paired stores, with 16-byte stores to rows that are 16- and 4-byte aligned."""
+    """Both sides of the rule that stores C through the caches or streams it, with 16-byte
+    stores to rows that are 16- and 4-byte aligned."""
     force(cap, 12)
     W = inputs.pattern_uniform(M, K, density, inputs.CFG_TEST, 7300 + M + K, 0.05)
     check(W, N, f"stores cap {cap} M {M} K {K}")
