@@ -60,22 +60,22 @@ typedef enum {
 /* Options for sdnn_plan_create; pass NULL for the defaults {0, 1, 0, 0, NULL, 0, 0}.
  *   panel_rows:   rows per register panel of the panel kernel.  0 (default) packs W four
  *                 times, with panels of 4, 12, 8 and 16 rows, and a fifth time with 32-row
- *                 panels for 128-column tiles unless tile_cols = 256; with tile_cols
- *                 and grouping 0 too (a default plan), also for the row-quad kernel, which
- *                 then serves sdnn_spmm and sdnn_conv3x3 (same result bit for bit; not where
- *                 the rows' entries lie so unevenly over K that the panel kernel is estimated
+ *                 panels for 128-column tiles unless tile_cols = 256; with tile_cols and
+ *                 grouping 0 too (a default plan), also for the row-quad kernel, which then
+ *                 serves sdnn_spmm and sdnn_conv3x3 (same result bit for bit; not where the
+ *                 rows' entries lie so unevenly over K that the panel kernel is estimated
  *                 to be as fast, nor products at an N where sdnn_plan_tune measured it
- *                 faster; sdnn_plan_launch_quads reports which).  The panel kernel, which also
- *                 serves the K-split calls and plans that fix panel_rows,
- *                 grouping or tile_cols, picks one packing per call: the 32-row panels (with 12
+ *                 faster; sdnn_plan_launch_quads reports which).  The panel kernel, which
+ *                 also serves the K-split calls and plans that fix panel_rows, grouping or
+ *                 tile_cols, picks one packing per call: the 32-row panels (with 12
  *                 consumer waves per workgroup) when W holds under 20 entries per 16 rows
  *                 and 32 columns and their grid fills the compute units; otherwise the
  *                 fewest rounds of workgroups over the compute units, then the most units
  *                 busy, then the shortest panels averaging at least 8 entries per 32
  *                 columns of W (4-row panels are not used below 8); sdnn_plan_tune can
  *                 replace that choice by a timed one, and sdnn_plan_launch_shape reports
- *                 it. 4, 8, 12 or 16 packs that
- *                 height only; 32 too, with tile_cols = 128 (else SDNN_ERR_DIM).
+ *                 it.  4, 8, 12 or 16 packs that height only; 32 too, with tile_cols = 128
+ *                 (else SDNN_ERR_DIM).
  *   permute:      1 = apply Algorithm 1 (default), 0 = identity order (ablation),
  *                 2 = panel-balancing order: rows, by nonzero count descending, each
  *                 go to the 4-row panel with the fewest nonzeros so far that has room,

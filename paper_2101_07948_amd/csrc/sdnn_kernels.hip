@@ -1,5 +1,6 @@
 // gfx950 kernels of the sparse-weight x dense-activation product (SparseDNN, arXiv
-// 2101.07948, Sec. 3.2.2) and the dense FP32 comparison GEMM (Sec. 3.2.1).
+// 2101.07948, Sec. 3.2.2) and the dense FP32 comparison GEMM (Sec. 3.2.1).  (Most products and
+// convolutions on default plans run on the row-quad kernel of sdnn_quad.hip: see on_quads.)
 //
 // Sparse kernel ("panel kernel").  The paper's microkernel walks the nonzeros of a
 // slice of the sparse matrix, broadcasts each nonzero into vector registers and
@@ -608,7 +609,11 @@ namespace {
 // ds_read_b128 rate of one CU).  t_launch = 4 us, bw = 4 TB/s (the partials mostly sit
 // in the Infinity Cache); all measured on MI355X.  A count is tried only if runs of
 // ceil(nseg / count) segments give exactly it, and replaces a smaller one only if it
-// costs at least 10 % less (the model's error on MI355X is about that size).
+// costs at least 10 % less (the model's error on MI355X is about that size).  (Every count
+// is priced on the panel kernel's 256-column launch.  A count of one runs on the row-quad
+// kernel of default plans, which is faster than its price here; the counts have been kept,
+// because more runs have the smaller rounding error: 768 x 3072, N = 1024 1.7e-7 of the
+// result against 3.2e-7.)
 constexpr int kMaxAutoSplits = 32;  // more runs than this never paid for their partials
 
 int choose_splits(const sdnn_plan_s* p, int N, bool conv) {

@@ -20,14 +20,15 @@
 //   * Each row sums its entries in ascending column order with fused multiply-adds, as in
 //     every kernel of the library, so C is the same bit for bit.
 //
-// What bounds it: LDS.  Every entry reads 16 bytes of B per four columns, 1 KB per quad-step
-// (four entries x 64 columns), 4.05 cycles of a CU's LDS; the FMAs, address and weight ops of a
-// quad-step take 16.4 cycles of a SIMD (a quarter of the CU) in groups of 4 lanes and 22.7 in
-// groups of 16, so the groups of 4 run at LDS's pace (the 768 x 3072 layer at 90 %, N = 4096:
-// LDS active in 76 % of the kernel's cycles, no bank conflicts) and are taken where a workgroup
-// has rows enough to fill its waves with them.  Measured against the panel kernel: that layer
-// 66.4 -> 47.3 us, 768 x 768 at 90 %, N = 1024 13.6 -> 8.4 us, 2048 x 2048 at 70 %, N = 512
-// 56.0 -> 36.2 us, 3072 x 768 at 97 %, N = 16384 with GELU 124.2 -> 108.6 us.
+// What bounds it: no unit alone.  A quad-step (four entries x 64 columns) reads 1 KB of B, 4.05
+// cycles of a CU's LDS, and its FMAs, address and weight ops take 16.4 cycles of a SIMD (a quarter
+// of the CU) in groups of 4 lanes and 22.7 in groups of 16, so the groups of 4 are taken where a
+// workgroup has rows enough to fill its waves with them.  On the 768 x 3072 layer at 90 %, N = 4096
+// (97 k cycles) the steps are 66 % of the SIMDs' time and their reads 65 % of LDS's, fillers
+// included, with no bank conflicts; waves wait 31 % of theirs, and each CU has one item, whose start
+// and drain nothing overlaps.  Smaller calls wait more (768 x 768, N = 1024: 54 %).  Measured against
+// the panel kernel: that layer 66.5 -> 46.8-48.8 us, 768 x 768 at 90 %, N = 1024 13.6 -> 8.3 us, 2048 x
+// 2048 at 70 %, N = 512 55.9 -> 36.1 us, 3072 x 768 at 97 %, N = 16384 with GELU 124.1 -> 100.1 us.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <stdlib.h>
@@ -520,7 +521,10 @@ hipError_t launch_stage(const DevQuads& d, const float* B, float* C, const float
 // the 256 MB memory-side cache does not hold: 3072 x 768 at 97 %, N = 16384 96 us streamed, 123
 // cached; 768 x 768 32 and 39; 3000 x 96 49 and 57; a small C is written back when the kernel
 // ends: 256 x 256 9.3 and 10.4), but for a K so small that the store is all there is to do
-// (3000 x 32 at 90 %, N = 16384: 54 and 49).
+// (3000 x 32 at 90 %, N = 16384: 54 and 49).  With still more buffers in turn, over 1 GiB, the half
+// lines cost what the step gains: that layer 151 us streamed, 128 cached, 123 on the panel kernel; 768 x
+// 768 36, 34 and 33.  (Two groups exchanging vectors, to store 128 bytes of a row at once: 125 us so,
+// but 110 instead of 100 with three sets.)
 bool cached_stores(const sdnn_plan_s* p, const float* C, int32_t N) {
   const int64_t bytes = (int64_t)p->M * N * 4;
   if (N % 16 != 0 || ((uintptr_t)C & 63) != 0) return bytes >= (int64_t)8 << 20;
